@@ -128,6 +128,23 @@ __device__ __forceinline__ void store4(float* p, float a, float b, float c, floa
   *reinterpret_cast<f32x4*>(p) = f32x4{a, b, c, d};
 }
 
+// Rows of a transposed 32x32 accumulator as bf16: entries i .. i + 7 (two groups
+// of four consecutive columns d = 8 (i / 4) + 4 (l / 32) + 0..3 of row l mod 32)
+// are exchanged between lanes l and l ^ 32 so that each lane stores 16
+// consecutive bytes; `row` is row l mod 32 from column 2 i + 8 (l / 32).
+__device__ __forceinline__ void store_rows16(__bf16* row, const f32x16& acc, int i) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 b2;
+  auto pk = [&](int e) {
+    b2 v;
+    v[0] = (__bf16)acc[e];
+    v[1] = (__bf16)acc[e + 1];
+    return __builtin_bit_cast(uint32_t, v);
+  };
+  const auto x = __builtin_amdgcn_permlane32_swap(pk(i), pk(i + 4), false, false);
+  const auto y = __builtin_amdgcn_permlane32_swap(pk(i + 2), pk(i + 6), false, false);
+  *reinterpret_cast<u32x4*>(row) = u32x4{x[0], y[0], x[1], y[1]};
+}
+
 __device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
 __device__ __forceinline__ float to_f32(float x) { return x; }
 
@@ -174,6 +191,14 @@ template <int N>
 __device__ __forceinline__ void wait_vmem() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// The same wait, ordered against every memory access around it: for a wave that
+// reads tiles it copied itself, with no barrier between.
+template <int N>
+__device__ __forceinline__ void wait_tiles() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // Workgroup barrier that leaves vector-memory operations (the asynchronous tile
@@ -234,6 +259,22 @@ struct TileCopy {
       asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(goff[ii]), "s"(gs),
                    "s"(lb + ii * NW * 64 * 16)
                    : "m0");
+  }
+  // The same copy piece by piece, between a wave's other work: `tie` is a value
+  // the piece is ordered after (its computation) and before (its use).
+  struct Cursor {
+    uint64_t gs;
+    uint32_t lb;
+  };
+  __device__ __forceinline__ Cursor cursor(const T* g, const T* lds) const {
+    return Cursor{uniform_addr(g), uniform_lds(lds) + lwave};
+  }
+  __device__ __forceinline__ float issue_piece(const Cursor& c, int ii, float tie) const {
+    asm volatile("s_mov_b32 m0, %3\n\tglobal_load_lds_dwordx4 %1, %2"
+                 : "+v"(tie)
+                 : "v"(goff[ii]), "s"(c.gs), "s"(c.lb + ii * NW * 64 * 16)
+                 : "m0", "memory");
+    return tie;
   }
 };
 

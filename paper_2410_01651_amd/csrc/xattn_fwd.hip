@@ -481,6 +481,316 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
   }
 }
 
+// ------------------------------ one wave per query chunk (bf16, k <= kWaveMaxK) ----
+//
+// The same products with the work split differently: a workgroup is one wave that
+// owns a whole query chunk, its 64 tokens as two halves of 32, and eight of them
+// share a CU (two waves per SIMD).  Against a pair of waves per chunk, a tile's K
+// and V^T fragments are read from LDS once for all 64 queries instead of once per
+// half, no barrier couples two waves, and one half's products can run beside the
+// other half's softmax (the longest phase: 32 exponentials per lane).
+//
+// K and V each have one LDS tile, filled by asynchronous copies issued piece by piece
+// between the products and the exponentials: V's during the score products of the tile
+// itself (its last reader was the tile before), the next K's during the first half's
+// softmax (the K fragments sit in registers by then).  Everything that a chunk switch
+// needs is found one chunk ahead: the landmark row comes by an asynchronous copy and its
+// fusion weights stay in registers (lane s: slot s), so the loop holds no load that the
+// compiler would wait for behind the copies.  The next chunk's queries are loaded after
+// the last score products and waited for with the next keys.
+//
+// What bounds it: the waves' issue (VALU 0.54, matrix cores 0.28, both 0.11 of the
+// SIMD cycles at 16K) under the board's power limit (the clock falls to 1.7-2.0 GHz as
+// it gets denser); the copies are waited for 8 % of a tile's time.
+// Measured, MI355X, the launch alone, pair form above -> this: 64K tokens (B = 2,
+// H = 16, k = 8) 549 -> 487 us, 16K (B = 8, H = 12) 459 -> 411 us, 1M (H = 8, bound by
+// the gather past the L2) 2,580 -> 2,540 us.  One wave per SIMD (512 registers, tiles two
+// ahead, every product under a softmax) took 524 and 410 us: nothing hides a chunk
+// switch there.  Lists longer than kWaveMaxK stay with the pair form: their
+// log-sum-exps do not fit in LDS beside the tiles (8 x 20 KiB per CU), and storing them
+// per item made this form no faster (k = 16: 339 us against 336 us).
+constexpr int kWaveMaxK = 8;
+constexpr int kWavesPerCu = 8;
+template <bool OBO>
+__global__ __launch_bounds__(64, 2) void xattn_fwd_wave_kernel(FwdParams p) {
+  using T = __bf16;
+  constexpr int TILE = kS * kD;
+  constexpr uint32_t kTileB = TILE * sizeof(T), kRowB = kD * sizeof(T);
+  __shared__ __attribute__((aligned(16))) T ring[2 * TILE];  // K tile, V tile
+  __shared__ int sMj[32];          // the next landmark row's chunks and scores
+  __shared__ float sMs[32];
+  __shared__ float sLse[2][32 * kWaveMaxK];  // per half: its 32 tokens x K log-sum-exps
+
+  const int lane = threadIdx.x & 63, hh = lane >> 5, l32 = lane & 31;
+  // (all counts below fit 32 bits: the launcher's work items and landmark rows do)
+  const int S = (int)(gridDim.x >> 3), st = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
+  const int nQ = (int)p.nQ, nKV = (int)p.nKV, H = p.H;
+  const StreamOrder ord(S, st, xcd, p.nwork, p.windows);
+  const int my_n = __builtin_amdgcn_readfirstlane((int)ord.length());
+  if (my_n == 0) return;
+  const int K = p.topk;
+  const float sc = p.attn_scale * kLog2e;
+  const int cb = 16 * ((lane >> 4) & 1);
+  const T* const gq = reinterpret_cast<const T*>(p.q);
+  T* const go = reinterpret_cast<T*>(p.out);
+
+  // ---- the stream's chunks, found one ahead of the copies: position pos of the
+  // stream is work item wd, chunk cd of (batch, head) bd * H + hd
+  int pos = 0, wd = __builtin_amdgcn_readfirstlane((int)ord.item(0));
+  int cd = wd % nQ, bd = wd / nQ / H, hd = wd / nQ % H;
+  auto row_of = [&]() { return (int64_t)(p.Hr == 1 ? bd : bd * H + hd) * nQ + (p.causal ? cd - 1 : 0); };
+  auto fetch_meta = [&]() {
+    if (pos < my_n && (!p.causal || cd > 0)) {
+      const int64_t ro = row_of() * K;
+      if (lane < K) {
+        dma_column_s(reinterpret_cast<const float*>(p.idx) + ro, (uint32_t)lane * 4, reinterpret_cast<float*>(sMj));
+        dma_column_s(p.sel + ro, (uint32_t)lane * 4, sMs);
+      }
+    }
+  };
+  // A query chunk with something to attend to: its work item, (batch, head), mask
+  // of valid slots, and in lane s < K slot s's key chunk and fusion weight.
+  struct Chunk {
+    int w, bh;
+    uint32_t mask;
+    int j;
+    float wt;
+  };
+  auto discover = [&](Chunk& x) {  // the next such chunk of the stream; false at its end
+    bool found = false;
+    while (!found && pos < my_n) {
+      const bool has = !p.causal || cd > 0, owner = p.Hr != 1 || hd == 0;
+      const bool in = has && lane < K;
+      const int mj = in ? sMj[l32] : -1;
+      const float ms = in ? sMs[l32] : 0.f;
+      const bool valid = in && mj >= 0 && mj < nKV;
+      const uint64_t mask = __ballot(valid);
+      // the valid lanes (slots) all sit in the lower half
+      const float mx = max64(valid ? ms : -INFINITY);
+      const float e = valid ? expf(ms - mx) : 0.f;
+      const float sum = sum32(e);
+      const float wv = valid ? e / sum : 0.f;
+      if (p.w && owner && in) p.w[row_of() * K + lane] = wv;
+      x.w = wd;
+      x.bh = bd * H + hd;
+      x.mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)mask);
+      x.j = mj;
+      x.wt = wv;
+      found = x.mask != 0;
+      if (!found) {
+        // nothing retrieved: zero output
+        const int64_t tok = (int64_t)wd * kS;
+#pragma unroll 1
+        for (int e2 = lane; e2 < kS * kD / 8; e2 += 64)
+          *reinterpret_cast<u32x4*>(go + tok * kD + e2 * 8) = u32x4{0, 0, 0, 0};
+        if (p.lse)
+#pragma unroll 1
+          for (int e2 = lane; e2 < kS * K; e2 += 64) p.lse[tok * K + e2] = -INFINITY;
+        if (p.w && p.causal && cd == 0 && owner) {
+          // the causal last row feeds no chunk: its weights go out with chunk 0
+          float w2;
+          int j2;
+          const int64_t last = ((int64_t)(p.Hr == 1 ? bd : bd * H + hd) * nQ + nQ - 1) * K;
+          wave_row_weight(p.idx, p.sel, last, K, nKV, w2, j2);
+          if (lane < K) p.w[last + lane] = w2;
+        }
+      }
+      if (++pos < my_n) {
+        if (p.windows) {
+          wd = __builtin_amdgcn_readfirstlane((pos * 8 + ((xcd + pos) & 7)) * S + st);
+          cd = wd % nQ;
+          bd = wd / nQ / H;
+          hd = wd / nQ % H;
+        } else {
+          wd += S;
+          cd += S;
+          while (cd >= nQ) {
+            cd -= nQ;
+            if (++hd == H) {
+              hd = 0;
+              ++bd;
+            }
+          }
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // sMj / sMs have been read
+      fetch_meta();
+      if (!found) wait_tiles<0>();  // the next row's chunks and scores
+    }
+    return found;
+  };
+  fetch_meta();
+  wait_tiles<0>();
+  Chunk x0, x1;
+  if (!discover(x0)) return;
+  wait_tiles<0>();
+  bool more = discover(x1);
+  if (!more) x1 = x0;
+  auto tile_of = [&](const Chunk& x, uint32_t rest) {  // element offset of the K and V tiles of the first slot in rest
+    const int j = min(max(__builtin_amdgcn_readlane(x.j, __builtin_ctz(rest)), 0), nKV - 1);
+    return ((int64_t)x.bh * nKV + j) * TILE;
+  };
+
+  const TileCopy<T, 1> cp(0, lane);
+  const T* const gk = reinterpret_cast<const T*>(p.k);
+  const T* const gv = reinterpret_cast<const T*>(p.v);
+  const lds_char* const lds0 = (const lds_char*)(ring);
+  uint32_t kofs[4], vofs[2][2];
+  {
+    const int s16 = lane & 15;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) kofs[kb] = Swz<T>::off(l32, 16 * kb + 8 * hh) * sizeof(T);
+#pragma unroll
+    for (int dh = 0; dh < 2; ++dh)
+#pragma unroll
+      for (int r8 = 0; r8 < 2; ++r8)
+        vofs[dh][r8] = kTileB + Swz<T>::off(8 * r8 + 4 * hh + (s16 >> 2), 32 * dh + cb + 4 * (s16 & 3)) * sizeof(T);
+  }
+
+  uint32_t rest = x0.mask;  // the current chunk's slots still to do
+  Frag<T> qa[4], qb[4];
+  const uint32_t qoff = (uint32_t)(l32 * kD + 8 * hh);  // this lane's part of 32 query rows
+  auto load_q = [&](int w) {
+    const T* r = gq + (int64_t)w * kS * kD;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      qa[kb] = load_frag(r + (qoff + 16 * kb));
+      qb[kb] = load_frag(r + (qoff + 32 * kD + 16 * kb));
+    }
+  };
+  load_q(x0.w);
+  int64_t off_v = tile_of(x0, rest);
+  {
+    cp.issue(gk + off_v, ring);
+  }
+  f32x16 oa0 = zero16(), oa1 = zero16(), ob0 = zero16(), ob1 = zero16();
+  f32x16 sa0, sa1, sb0, sb1;
+  Frag<T> kf[8], vf[8], pa[4], pb[4];
+  auto read_k = [&]() {
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      kf[2 * kb] = lds_b128_at(lds0 + kofs[kb]);
+      kf[2 * kb + 1] = lds_b128_at(lds0 + kofs[kb] + 32 * kRowB);
+    }
+  };
+  auto read_v = [&]() {
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      vf[2 * kb] = lds_tr2(lds0 + vofs[0][0] + 16 * kb * kRowB, lds0 + vofs[0][1] + 16 * kb * kRowB);
+      vf[2 * kb + 1] = lds_tr2(lds0 + vofs[1][0] + 16 * kb * kRowB, lds0 + vofs[1][1] + 16 * kb * kRowB);
+    }
+  };
+  // One half's softmax over the tile's 64 keys; part(i, mx) is called eight times
+  // between the exponentials, which take the mx it leaves (it orders what it issues).
+  auto softmax = [&](f32x16& s0, f32x16& s1, int half, int s, float wt, Frag<T>* pf, auto part) {
+    float mx = max_xor32(max_of(s0, s1)) * sc;
+    if (OBO) mx = fmaxf(mx, 0.f);
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      part(i, mx);
+#pragma unroll
+      for (int e = 2 * i; e < 2 * i + 2; ++e) {
+        s0[e] = __builtin_amdgcn_exp2f(fmaf(s0[e], sc, -mx));
+        s1[e] = __builtin_amdgcn_exp2f(fmaf(s1[e], sc, -mx));
+      }
+      sum += (s0[2 * i] + s1[2 * i]) + (s0[2 * i + 1] + s1[2 * i + 1]);
+    }
+    sum = sum_xor32(sum);
+    if (OBO) sum += __builtin_amdgcn_exp2f(-mx);
+    // both lanes of a query hold the same value
+    sLse[half][l32 * K + s] = (mx + __builtin_amdgcn_logf(sum)) * kLn2;
+    const float coef = wt * __builtin_amdgcn_rcpf(sum);
+    frag_from_acc(pf[0], s0, 0, coef);
+    frag_from_acc(pf[1], s0, 1, coef);
+    frag_from_acc(pf[2], s1, 0, coef);
+    frag_from_acc(pf[3], s1, 1, coef);
+  };
+  auto store_half = [&](int half, f32x16& o0_, f32x16& o1_) {
+    const int64_t tok = (int64_t)x0.w * kS + 32 * half;
+    T* orow = go + tok * kD;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      store_rows16(orow + (qoff + 16 * m), o0_, 8 * m);
+      store_rows16(orow + (qoff + 32 + 16 * m), o1_, 8 * m);
+    }
+    if (p.lse) {
+      const uint32_t full = (1u << K) - 1u;
+#pragma unroll 1
+      for (int s = 0; x0.mask != full && s < K; ++s)
+        if (!((x0.mask >> s) & 1u)) sLse[half][l32 * K + s] = -INFINITY;
+      float v[kWaveMaxK / 2];
+#pragma unroll
+      for (int i = 0; i < kWaveMaxK / 2; ++i) v[i] = sLse[half][64 * i + lane];
+      float* lse = p.lse + tok * K;
+#pragma unroll
+      for (int i = 0; i < kWaveMaxK / 2; ++i)
+        if (64 * i + lane < 32 * K) lse[(uint32_t)(64 * i + lane)] = v[i];
+    }
+    o0_ = zero16();
+    o1_ = zero16();
+  };
+
+  while (true) {
+    const int s = __builtin_ctz(rest);
+    const float wt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x0.wt), s));
+    rest &= rest - 1u;
+    const bool last = rest == 0u;
+    // the next item (past the last one: a copy nothing reads)
+    const int64_t off = last ? tile_of(x1, x1.mask) : tile_of(x0, rest);
+    sa0 = zero16();
+    sa1 = zero16();
+    sb0 = zero16();
+    sb1 = zero16();
+    wait_tiles<0>();  // this item's keys
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(qa[i]), "+v"(qb[i]));
+    read_k();
+    {
+      const typename TileCopy<T, 1>::Cursor cv = cp.cursor(gv + off_v, ring + TILE);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (i & 1) mma32(sa1, kf[i], qa[i >> 1]);
+        else mma32(sa0, kf[i], qa[i >> 1]);
+        cp.issue_piece(cv, i, sc);
+      }
+    }
+    const typename TileCopy<T, 1>::Cursor ck = cp.cursor(gk + off, ring);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this item's keys have been read
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i & 1) mma32(sb1, kf[i], qb[i >> 1]);
+      else mma32(sb0, kf[i], qb[i >> 1]);
+    }
+    softmax(sa0, sa1, 0, s, wt, pa, [&](int i, float& mx) { mx = cp.issue_piece(ck, i, mx); });
+    if (last) load_q(x1.w);
+    if (last) wait_tiles<16>();
+    else wait_tiles<8>();  // this item's values
+    read_v();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i & 1) mma32(oa1, vf[i], pa[i >> 1]);
+      else mma32(oa0, vf[i], pa[i >> 1]);
+    }
+    softmax(sb0, sb1, 1, s, wt, pb, [&](int, float&) {});
+    off_v = off;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i & 1) mma32(ob1, vf[i], pb[i >> 1]);
+      else mma32(ob0, vf[i], pb[i >> 1]);
+    }
+    if (last) {
+      store_half(0, oa0, oa1);
+      store_half(1, ob0, ob1);
+      if (!more) break;
+      x0 = x1;
+      rest = x0.mask;
+      more = discover(x1);
+    }
+  }
+  wait_tiles<0>();  // no copy outlives the workgroup's LDS
+}
+
 }  // namespace
 
 hipError_t launch_xattn_fwd(const Shape& s, const void* q, const void* k, const void* v,
@@ -503,6 +813,15 @@ hipError_t launch_xattn_fwd(const Shape& s, const void* q, const void* k, const 
   const int64_t target = round8((int64_t)device_cus() * kWgPerCu), wgs = (p.nwork + kPairs - 1) / kPairs;
   const dim3 grid((unsigned)(wgs < target ? round8(wgs) : target)), block(kThreads);
   auto go = [&](auto kernel) { launch_kernel("xattn_fwd_kernel", kernel, grid, block, 0, stream, p); };
+  // one wave per chunk for short lists in bf16 (see there); the LMK row's extra state
+  // does not fit its registers
+  if (s.bf16 && !xr && s.topk <= kWaveMaxK) {
+    const int64_t waves = round8((int64_t)device_cus() * kWavesPerCu);
+    const dim3 wgrid((unsigned)(p.nwork < waves ? round8(p.nwork) : waves));
+    auto wave = [&](auto kernel) { launch_kernel("xattn_fwd_kernel", kernel, wgrid, dim3(64), 0, stream, p); };
+    s.off_by_one ? wave(xattn_fwd_wave_kernel<true>) : wave(xattn_fwd_wave_kernel<false>);
+    return take_launch_error();
+  }
   if (s.bf16) {
     if (xr) s.off_by_one ? go(xattn_fwd_kernel<__bf16, true, true>) : go(xattn_fwd_kernel<__bf16, false, true>);
     else s.off_by_one ? go(xattn_fwd_kernel<__bf16, true, false>) : go(xattn_fwd_kernel<__bf16, false, false>);

@@ -1,0 +1,70 @@
+"""Two kernel forms of the same step against each other, at the sizes where a form's
+own indexing can go wrong.  The forms do the same arithmetic in fp32 from the same
+bf16 products, so they differ by the rounding of bf16 probabilities and outputs."""
+
+import numpy as np
+import pytest
+
+from _helpers import ensure_built, host64, max_abs_rel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ensure_built()
+    return torch.device("cuda:0")
+
+
+def _lists(rng, rows, nC, k, holes):
+    """Random retrieval lists of `rows` x nC landmark rows (row t among chunks < t), with
+    pads in the middle, rows that are all pads and an out-of-range index when `holes`."""
+    idx = np.full((rows, nC, k), -1, np.int32)
+    sel = np.full((rows, nC, k), -np.inf, np.float32)
+    for r in range(rows):
+        for t in range(1, nC):
+            n = min(t, k)
+            js = np.sort(rng.choice(t, size=n, replace=False))
+            if holes and t % 5 == 0:
+                js[rng.integers(n)] = -1
+            if holes and t % 7 == 0:
+                js[:] = -1
+            idx[r, t, :n] = js
+            sel[r, t, :n] = np.where(js >= 0, rng.standard_normal(n), -np.inf)
+    if holes and nC > 9:
+        idx[0, 9, 0] = nC + 3
+    return idx, sel
+
+
+@pytest.mark.parametrize("B,H,Hr,nC,k,holes,obo", [
+    (1, 1, 1, 1, 3, False, False),        # one chunk, nothing retrieved
+    (1, 2, 1, 11, 1, True, False),        # one slot per chunk: a chunk switch every tile
+    (2, 3, 3, 13, 5, True, True),
+    (1, 3, 1, 700, 8, True, False),       # more items than resident streams
+    (1, 1, 1, 2100, 8, False, False),     # window order
+])
+def test_forward_wave_form_equals_pair_form(dev, B, H, Hr, nC, k, holes, obo):
+    """bf16 lists of up to 8 run on one wave per chunk; the same lists padded to 9 slots
+    run on a pair of waves per chunk."""
+    import torch
+    from paper_2410_01651_amd import gca
+    rng = np.random.default_rng(nC + k)
+    idx, sel = _lists(rng, B * Hr, nC, k, holes)
+    g = torch.Generator(device=dev).manual_seed(nC)
+    q, kk, v = (torch.randn(B, H, nC * 64, 64, generator=g, device=dev, dtype=torch.bfloat16) for _ in range(3))
+    got = []
+    for K in (k, 9):
+        p = gca.problem(B, H, nC, K, Hr=Hr, D=64, off_by_one=obo)
+        i = np.full((B, Hr, nC, K), -1, np.int32)
+        s = np.full((B, Hr, nC, K), -np.inf, np.float32)
+        i[..., :k] = idx.reshape(B, Hr, nC, k)
+        s[..., :k] = sel.reshape(B, Hr, nC, k)
+        out, lse, w = gca.grouped_xattn_fwd(p, q, kk, v, torch.from_numpy(i).to(dev), torch.from_numpy(s).to(dev))
+        got.append((host64(out), host64(lse)[..., :k], host64(w)[..., :k]))
+    (o0, l0, w0), (o1, l1, w1) = got
+    assert max_abs_rel(o0, o1) <= 2.0 ** -7    # two bf16 roundings of sums that differ in bf16 probabilities
+    assert max_abs_rel(l0, l1) <= 1e-6
+    assert max_abs_rel(w0, w1) <= 1e-6
