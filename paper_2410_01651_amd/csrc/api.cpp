@@ -140,6 +140,27 @@ size_t forward_ws(const gca_problem* p, const gca::Shape& s) {
   return gca::align256(sizeof(float) * (size_t)s.B * s.Hr * s.nQ * s.nKV);
 }
 
+// Scratch for selecting on landmarks too wide for registers without the score matrix:
+// the output, which the attention writes only afterwards, or null (the launcher then
+// takes its slower form that needs none) where it overlaps another argument.
+void* wide_scratch(const gca::Shape& s, const void* lmk_q, const void* lmk_k, const void* q, const void* k,
+                   const void* v, void* out, const int32_t* idx, const float* sel) {
+  const size_t need = gca::wide_select_bytes(s), e = s.bf16 ? 2 : 4;
+  const size_t row = (size_t)gca::kChunk * e, BH = (size_t)s.B * s.H, rows = (size_t)s.B * s.Hr * s.nQ;
+  if (need == 0 || need > BH * s.nQ * s.Sq * row) return nullptr;
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(out), hi = lo + need;
+  auto clear_of = [&](const void* p, size_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    return a >= hi || a + bytes <= lo;
+  };
+  const size_t kv = BH * s.nKV * gca::kChunk * row;
+  return clear_of(lmk_q, rows * s.D * e) && clear_of(lmk_k, (size_t)s.B * s.Hr * s.nKV * s.D * e) &&
+                 clear_of(q, BH * s.nQ * s.Sq * row) && clear_of(k, kv) && clear_of(v, kv) &&
+                 clear_of(idx, rows * s.topk * sizeof(int32_t)) && clear_of(sel, rows * s.topk * sizeof(float))
+             ? out
+             : nullptr;
+}
+
 gca_status check_ws(void* ws, size_t have, size_t need) {
   if (need == 0) return GCA_OK;
   if (!ws) return fail(GCA_ERR_WORKSPACE, "workspace is NULL, need " + std::to_string(need) + " bytes");
@@ -333,7 +354,10 @@ static gca_status forward_dispatch(const gca_problem* p, const gca::Shape& s, co
                                              w, lmk_q, lmk_k, stream),
                     "gca_forward (decode attention)");
   } else if (fused_path(p, s)) {
-    e = gca::launch_fused_select(s, lmk_q, lmk_k, idx, sel, workspace, stream);
+    void* scratch = gca::select_plan(s).tile == gca::kWideTile
+                        ? wide_scratch(s, lmk_q, lmk_k, q, k, v, out, idx, sel)
+                        : workspace;
+    e = gca::launch_fused_select(s, lmk_q, lmk_k, idx, sel, scratch, stream);
   } else {
     float* scores = reinterpret_cast<float*>(workspace);
     e = gca::launch_chunk_scores(s, lmk_q, lmk_k, scores, stream);

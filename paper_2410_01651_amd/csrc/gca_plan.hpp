@@ -56,10 +56,12 @@ int* decode_list_chunks(const Shape& s, void* ws);
 // such lists (list number = class * parts_max + part).
 constexpr int kSelRows = 128;
 constexpr int kSelTile = 32;
+constexpr int kWideTile = 128;  // key chunks per tile for landmarks too wide for registers
 constexpr int kSelClasses = 8;
 struct SelectPlan {
   bool split;            // the split form applies (else one pass per row block, no workspace)
   int64_t blocks;        // row blocks per (batch, retrieval head)
+  int tile;              // key chunks per tile: kSelTile or kWideTile
   int64_t tiles;         // key tiles
   int tiles_per_part;
   int64_t parts_max;     // parts of one class in the largest row block
@@ -67,7 +69,8 @@ struct SelectPlan {
   int64_t items_per_class;  // work items of one class per (batch, retrieval head)
 };
 SelectPlan select_plan(const Shape& s);
-size_t fused_workspace(const Shape& s);
+size_t fused_workspace(const Shape& s);    // narrow landmarks (0 for wide ones)
+size_t wide_select_bytes(const Shape& s);  // wide landmarks' scratch (0 for narrow ones)
 
 // Backward workspace: fusion weights, per-(token, slot) values of the
 // query-stationary pass, dw partials and the inverse index (CSR) of the
@@ -108,8 +111,9 @@ hipError_t launch_decode_scan(const Shape& s, const void* lmk_q, const void* lmk
 hipError_t launch_xattn_decode(const Shape& s, const float* list_s, const int* list_j, const void* q,
                                const void* k, const void* v, int32_t* idx, float* sel, void* out, float* lse,
                                float* w, const void* lmk_q, const void* lmk_k, hipStream_t stream);
-// Causal: scores and top-k without the score matrix (workspace: fused_workspace),
-// split over key-tile parts when select_plan(s).split ...
+// Causal: scores and top-k without the score matrix, split over key-tile parts when
+// select_plan(s).split (ws: fused_workspace or wide_select_bytes bytes; for wide
+// landmarks it may be null, which takes the next form) ...
 hipError_t launch_fused_select(const Shape& s, const void* lmk_q, const void* lmk_k, int32_t* idx,
                                float* sel, void* ws, hipStream_t stream);
 // ... else one pass per 64-row block (no workspace).

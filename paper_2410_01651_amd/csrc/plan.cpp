@@ -60,24 +60,35 @@ int* decode_list_chunks(const Shape& s, void* ws) {
 
 SelectPlan select_plan(const Shape& s) {
   SelectPlan p{};
-  // landmark queries stay in registers (bf16 up to 512 columns, fp32 up to 256)
-  // next to each lane's best-16 list at most
-  p.split = s.causal && s.topk <= 16 && (s.bf16 ? s.D <= 512 : s.D <= 256);
+  // landmark queries stay in registers (bf16 up to 512 columns, fp32 up to 256) next
+  // to each lane's best-16 list at most; wider ones are staged through LDS in tiles of
+  // kWideTile keys
+  const bool wide = s.bf16 ? s.D > 512 : s.D > 256;
+  p.split = s.causal && s.topk <= 16;
   p.blocks = (s.nQ + kSelRows - 1) / kSelRows;
-  p.tiles = (s.nKV + kSelTile - 1) / kSelTile;
-  p.tiles_per_part = 64;  // a power of two
-  if (!p.split) return p;
+  p.tile = wide ? kWideTile : kSelTile;
+  p.tiles = (s.nKV + p.tile - 1) / p.tile;
+  // tiles per part, a power of two.  Narrow: 2,048 keys.  Wide: 1,024 (a tile is twice
+  // the work or more), and as many as it takes for a row's lists and threshold to fit
+  // in the space of one query chunk of one head (their scratch is the output).
+  p.tiles_per_part = wide ? 8 : 64;
   // the largest row block needs every key tile
   const int64_t per_class = (p.tiles + kSelClasses - 1) / kSelClasses;
-  p.parts_max = (per_class + p.tiles_per_part - 1) / p.tiles_per_part;
-  if (p.parts_max < 1) p.parts_max = 1;
-  p.lists = kSelClasses * p.parts_max;
+  for (;; p.tiles_per_part *= 2) {
+    p.parts_max = (per_class + p.tiles_per_part - 1) / p.tiles_per_part;
+    if (p.parts_max < 1) p.parts_max = 1;
+    p.lists = kSelClasses * p.parts_max;
+    if (!wide || p.parts_max == 1 ||
+        p.lists * s.topk * 8 + 64 <= (int64_t)kChunk * kChunk * (s.bf16 ? 2 : 4))
+      break;
+  }
+  if (!p.split) return p;
   // items of one class: sum over row blocks of its parts there
   int64_t items = 0;
   for (int64_t r = 0; r < p.blocks; ++r) {
     // row block r reaches key chunks below its last row: tiles [0, nt)
     const int64_t last_row = (r + 1) * kSelRows - 1 < s.nQ - 1 ? (r + 1) * kSelRows - 1 : s.nQ - 1;
-    int64_t nt = (last_row - 1) / kSelTile + 1;  // key chunks j <= last_row - 1
+    int64_t nt = (last_row - 1) / p.tile + 1;  // key chunks j <= last_row - 1
     if (last_row < 1) nt = 0;
     if (nt > p.tiles) nt = p.tiles;
     const int64_t c0 = nt > 0 ? (nt + kSelClasses - 1) / kSelClasses : 0;  // class 0 has the most tiles
@@ -87,13 +98,23 @@ SelectPlan select_plan(const Shape& s) {
   return p;
 }
 
-size_t fused_workspace(const Shape& s) {
-  const SelectPlan p = select_plan(s);
-  if (!p.split) return 0;
+namespace {
+size_t select_bytes(const Shape& s, const SelectPlan& p) {
   const size_t n = (size_t)s.B * s.Hr * s.nQ * p.lists * s.topk;
   // the lists' scores and chunks, then one published threshold per row
   return align256(n * sizeof(float)) + align256(n * sizeof(int)) +
          align256(sizeof(uint32_t) * (size_t)s.B * s.Hr * s.nQ);
+}
+}  // namespace
+
+size_t fused_workspace(const Shape& s) {
+  const SelectPlan p = select_plan(s);
+  return p.split && p.tile == kSelTile ? select_bytes(s, p) : 0;
+}
+
+size_t wide_select_bytes(const Shape& s) {
+  const SelectPlan p = select_plan(s);
+  return p.split && p.tile == kWideTile ? select_bytes(s, p) : 0;
 }
 
 // --------------------------------------------------------- backward ----

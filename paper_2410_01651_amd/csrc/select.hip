@@ -39,7 +39,7 @@ static_assert(kSelWaves * 32 == kSelRows, "one 32-row column block per wave");
 struct SelParams {
   uint32_t* gthr;  // per landmark row: the best published k-th score (order bits of a packed key), 0 = none
   int64_t nQ, nKV, tiles, blocks, items_per_class, parts_max, lists;
-  int D, K, tpp, tpp_shift;  // tiles per part, a power of two (parts need no division)
+  int D, K, tile, tpp, tpp_shift;  // keys per tile; tiles per part, a power of two (parts need no division)
   float scale;
   uint64_t seed;
 };
@@ -48,11 +48,139 @@ struct SelParams {
 __device__ __forceinline__ int64_t sel_block_tiles(const SelParams& p, int64_t r) {
   const int64_t last = min((r + 1) * kSelRows - 1, p.nQ - 1);
   if (last < 1) return 0;
-  return min((last - 1) / kSelTile + 1, p.tiles);
+  return min((last - 1) / p.tile + 1, p.tiles);
 }
 // Tiles of class x among the first nt; parts they form.
 __device__ __forceinline__ int64_t sel_class_tiles(int64_t nt, int x) {
   return nt > x ? (nt - x + kSelClasses - 1) / kSelClasses : 0;
+}
+
+// Block -> (retrieval slice, class, row block, part): items of a class in order of
+// descending row block, so the longest items start first.  False: no such item.
+struct SelItem {
+  int64_t bhr, r, part;
+  int x, nu;  // class; tiles of the item
+};
+__device__ __forceinline__ bool sel_item(const SelParams& p, SelItem& it) {
+  it.x = (int)(blockIdx.x % kSelClasses);
+  const int64_t rest = blockIdx.x / kSelClasses;
+  it.bhr = rest / p.items_per_class;
+  int64_t i = rest % p.items_per_class;
+  for (it.r = p.blocks - 1; it.r >= 0; --it.r) {
+    const int64_t ncls = sel_class_tiles(sel_block_tiles(p, it.r), it.x);
+    const int64_t np = (ncls + p.tpp - 1) >> p.tpp_shift;
+    if (i < np) {
+      it.part = i;
+      it.nu = (int)min<int64_t>(p.tpp, ncls - i * p.tpp);
+      return true;
+    }
+    i -= np;
+  }
+  return false;  // this class has fewer items
+}
+
+// The row's threshold: the better k-th best of its two lanes' lists and of what
+// the row's other items have published (each is the score of a candidate beaten by
+// k - 1 others, so a candidate below it cannot be in the row's top k).  This lane
+// pair publishes its own with an atomic maximum, which returns the best published so
+// far; a value read late is only a weaker filter, never a wrong one.  Split in two so
+// that products can run while the atomic is away.
+template <int KM>
+__device__ __forceinline__ uint32_t sel_publish(const SelParams& p, const TopKeys<KM>& L, int64_t bhr, int64_t t,
+                                                uint32_t& own) {
+  uint32_t pa, pb;
+  pair32((uint32_t)(L.k[KM - 1] >> 32), pa, pb);
+  own = pa > pb ? pa : pb;
+  uint32_t pub = 0u;
+  if ((threadIdx.x & 32) == 0 && t < p.nQ && own != 0u)
+    pub = __hip_atomic_fetch_max(p.gthr + bhr * p.nQ + t, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return pub;
+}
+__device__ __forceinline__ float sel_threshold(uint32_t own, uint32_t pub) {
+  uint32_t qa, qb;
+  pair32(pub, qa, qb);
+  const uint32_t hi = max(own, max(qa, qb));  // the best threshold's score bits
+  return hi == 0u ? -INFINITY : key_score((uint64_t)hi << 32);
+}
+
+// Folds the 16 scores a lane holds of 32 keys from key0 (row t's, S^T in the
+// accumulator layout: register i holds key 8 (i / 4) + 4 hh + i % 4; four consecutive
+// keys per group of four registers, so one generator call gives their Gumbel noise)
+// into its list.  The candidates are filtered against the threshold into a bit mask;
+// then every lane inserts its surviving candidates one per round, so a round costs one
+// insert for the wave however many rows have a survivor, and the wave runs as many
+// rounds as its lane with the most survivors.  full: every key is a candidate.
+template <int KM, bool GUMBEL>
+__device__ __forceinline__ void sel_fold(const SelParams& p, TopKeys<KM>& L, f32x16 a, int64_t key0, int64_t bhr,
+                                         int64_t t, float ts, bool full) {
+  const int hh = (threadIdx.x >> 5) & 1;
+  uint32_t mask = 0u;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int64_t jg = key0 + 8 * g + 4 * hh;
+    f32x4 nz = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (GUMBEL) nz = gumbel_noise4(p.seed, (uint32_t)bhr, (uint32_t)t, (uint32_t)(jg >> 2));
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      a[4 * g + m] = a[4 * g + m] * p.scale + nz[m];
+      mask |= (uint32_t)(a[4 * g + m] >= ts) << (4 * g + m);
+    }
+  }
+  if (!full) {
+    // keys at or past the row (and rows past the end) are not candidates
+    const int64_t lim = t < p.nQ ? t - (key0 + 4 * hh) : 0;  // keys below the row, from this lane's first
+    uint32_t okm = 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) okm |= (uint32_t)(8 * (i >> 2) + (i & 3) < lim) << i;
+    mask &= okm;
+  }
+  while (__builtin_amdgcn_ballot_w64(mask != 0u)) {
+    if (mask != 0u) {
+      const int i = __builtin_ctz(mask);
+      mask &= mask - 1u;
+      // a[i] by a four-level select on the bits of i
+      float v8[8], v4[4], v2[2];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v8[e] = (i & 1) ? a[2 * e + 1] : a[2 * e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v4[e] = (i & 2) ? v8[2 * e + 1] : v8[2 * e];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) v2[e] = (i & 4) ? v4[2 * e + 1] : v4[2 * e];
+      const float v = (i & 8) ? v2[1] : v2[0];
+      L.insert(pack_key(v, (int)(key0 + 8 * (i >> 2) + 4 * hh + (i & 3))));
+    }
+  }
+}
+
+// The item's best k of row t: the partner lane's list entries inserted into this
+// lane's (the two lanes hold disjoint keys, so the partner's entry is the one that
+// differs from this lane's; equal entries are both empty), and stored.
+template <int KM>
+__device__ __forceinline__ void sel_store(const SelParams& p, TopKeys<KM>& L, const SelItem& it, int64_t t,
+                                          float* __restrict__ ls, int* __restrict__ lj) {
+  uint64_t pk[KM];
+#pragma unroll
+  for (int e = 0; e < KM; ++e) {
+    uint32_t la, lb, ha, hb;
+    pair32((uint32_t)L.k[e], la, lb);
+    pair32((uint32_t)(L.k[e] >> 32), ha, hb);
+    const bool own_first = la == (uint32_t)L.k[e] && ha == (uint32_t)(L.k[e] >> 32);
+    pk[e] = own_first ? ((uint64_t)hb << 32 | lb) : ((uint64_t)ha << 32 | la);
+  }
+#pragma unroll
+  for (int e = 0; e < KM; ++e)
+    if (pk[e] != 0) L.insert(pk[e]);
+  if ((threadIdx.x & 32) == 0 && t < p.nQ) {
+    const int64_t o = ((it.bhr * p.nQ + t) * p.lists + it.x * p.parts_max + it.part) * p.K;
+#pragma unroll
+    for (int e = 0; e < KM; ++e) {
+      if (e < p.K) {
+        const bool real = L.k[e] != 0;
+        ls[o + e] = real ? key_score(L.k[e]) : -INFINITY;
+        lj[o + e] = real ? key_chunk(L.k[e]) : -1;
+      }
+    }
+  }
 }
 
 // NCH: 64-column chunks of the landmark width (D / 64), a compile-time count so
@@ -66,24 +194,10 @@ __global__ __launch_bounds__(kSelThreads, 2) void select_part_kernel(const T* __
   static_assert(NCH >= 1 && NCH <= SelMax<T>::kCh, "landmark width held in registers");
   __shared__ __attribute__((aligned(16))) T stage[2 * NCH * TILE];
 
-  // block -> (retrieval slice, class, item); items of a class in order of
-  // descending row block, so the longest items start first
-  const int x = (int)(blockIdx.x % kSelClasses);
-  const int64_t rest = blockIdx.x / kSelClasses;
-  const int64_t bhr = rest / p.items_per_class;
-  int64_t it = rest % p.items_per_class;
-  int64_t r = p.blocks - 1, part = -1, ncls = 0;
-  for (; r >= 0; --r) {
-    ncls = sel_class_tiles(sel_block_tiles(p, r), x);
-    const int64_t np = (ncls + p.tpp - 1) >> p.tpp_shift;
-    if (it < np) {
-      part = it;
-      break;
-    }
-    it -= np;
-  }
-  if (part < 0) return;  // this class has fewer items
-  const int nu = (int)min<int64_t>(p.tpp, ncls - part * p.tpp);  // tiles of this item
+  SelItem it;
+  if (!sel_item(p, it)) return;
+  const int x = it.x, nu = it.nu;
+  const int64_t bhr = it.bhr, r = it.r, part = it.part;
   auto tile_of = [&](int u) -> int64_t { return x + kSelClasses * (part * p.tpp + u); };
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, l32 = lane & 31;
@@ -125,18 +239,8 @@ __global__ __launch_bounds__(kSelThreads, 2) void select_part_kernel(const T* __
     const int64_t j0 = tile_of(u) * kSelTile;  // first key chunk of the tile
     // wave-uniform: some (row, key) pair of this wave's block is a candidate
     if (j0 < t0w + 31 && t0w < p.nQ) {
-      // the row's threshold: the better k-th best of its two lanes' lists and of
-      // what the row's other items have published (each is the score of a
-      // candidate beaten by k - 1 others, so a candidate below it cannot be in
-      // the row's top k).  This lane pair publishes its own with an atomic
-      // maximum, which returns the best published so far; a value read late is
-      // only a weaker filter, never a wrong one.
-      uint32_t pa, pb;
-      pair32((uint32_t)(L.k[KM - 1] >> 32), pa, pb);
-      const uint32_t own = pa > pb ? pa : pb;
-      uint32_t pub = 0u;
-      if (hh == 0 && t < p.nQ && own != 0u)
-        pub = __hip_atomic_fetch_max(p.gthr + bhr * p.nQ + t, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t own;
+      const uint32_t pub = sel_publish(p, L, bhr, t, own);
       const T* sK = stage + (u & 1) * NCH * TILE;
       // S^T of the tile's 32 keys against the wave's 32 rows
       auto half_scores = [&](int key0) __device__ {
@@ -148,87 +252,113 @@ __global__ __launch_bounds__(kSelThreads, 2) void select_part_kernel(const T* __
         return a;
       };
       const f32x16 acc = half_scores(0);
-      uint32_t qa, qb;
-      pair32(pub, qa, qb);
-      const uint32_t hi = max(own, max(qa, qb));   // the best threshold's score bits
-      const float ts = hi == 0u ? -INFINITY : key_score((uint64_t)hi << 32);
+      const float ts = sel_threshold(own, pub);
       // full tile: every key below every row of the wave (and inside the keys)
       const bool full = j0 + kSelTile <= t0w && j0 + kSelTile <= p.nKV && t0w + 31 < p.nQ;
-      // accumulator register i holds key 8 (i / 4) + 4 hh + i % 4 of its 32-key half
-      // (four consecutive keys per group of four registers: one generator call
-      // gives their Gumbel noise).  A half's 16 candidates are filtered against
-      // the threshold into a bit mask; then every lane inserts its surviving
-      // candidates one per round, so a round costs one insert for the wave
-      // however many rows have a survivor, and the wave runs as many rounds as
-      // its lane with the most survivors.
-      auto fold_half = [&](f32x16 a, int half_key0) __device__ {
-        uint32_t mask = 0u;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int64_t jg = j0 + half_key0 + 8 * g + 4 * hh;
-          f32x4 nz = f32x4{0.f, 0.f, 0.f, 0.f};
-          if constexpr (GUMBEL) nz = gumbel_noise4(p.seed, (uint32_t)bhr, (uint32_t)t, (uint32_t)(jg >> 2));
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            a[4 * g + m] = a[4 * g + m] * p.scale + nz[m];
-            mask |= (uint32_t)(a[4 * g + m] >= ts) << (4 * g + m);
-          }
-        }
-        if (!full) {
-          // keys at or past the row (and rows past the end) are not candidates
-          const int64_t lim = t < p.nQ ? t - (j0 + half_key0 + 4 * hh) : 0;  // keys below the row, from this lane's first
-          uint32_t okm = 0u;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) okm |= (uint32_t)(8 * (i >> 2) + (i & 3) < lim) << i;
-          mask &= okm;
-        }
-        while (__builtin_amdgcn_ballot_w64(mask != 0u)) {
-          if (mask != 0u) {
-            const int i = __builtin_ctz(mask);
-            mask &= mask - 1u;
-            // a[i] by a four-level select on the bits of i
-            float v8[8], v4[4], v2[2];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v8[e] = (i & 1) ? a[2 * e + 1] : a[2 * e];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v4[e] = (i & 2) ? v8[2 * e + 1] : v8[2 * e];
-#pragma unroll
-            for (int e = 0; e < 2; ++e) v2[e] = (i & 4) ? v4[2 * e + 1] : v4[2 * e];
-            const float v = (i & 8) ? v2[1] : v2[0];
-            L.insert(pack_key(v, (int)(j0 + half_key0 + 8 * (i >> 2) + 4 * hh + (i & 3))));
-          }
-        }
-      };
-      fold_half(acc, 0);
+      sel_fold<KM, GUMBEL>(p, L, acc, j0, bhr, t, ts, full);
     }
   }
+  sel_store(p, L, it, t, ls, lj);
+}
 
-  // the row's best k: the partner lane's list entries inserted into this lane's
-  // (the two lanes hold disjoint keys, so the partner's entry is the one that
-  // differs from this lane's; equal entries are both empty)
-  uint64_t pk[KM];
+// Wide landmarks (their queries do not fit in registers): both operands go through
+// LDS.  An item is again 128 rows against its class's key tiles, here of kWideTile
+// keys; wave w owns 32 rows and computes S^T of all 128 keys against them, so a row's
+// candidates stay in one wave's two lanes as above.  The landmark width is walked in
+// 64-column chunks of both operands, two stages deep, the next chunk (the next tile's
+// first included) in flight during the current one's products.
+//
+// Bound by the LDS: per chunk a wave reads 4 + 16 fragments for 16 products (2 waves
+// per SIMD: about 1,250 LDS cycles against 1,024 of the matrix cores).  12,288 landmark
+// rows of width 1,024: 2,370 us for the one-pass form (fused_select_kernel, 192
+// workgroups there) -> 420 us (370 TFLOP/s) + 24 us for the merge.
+template <typename T, int KM, bool GUMBEL>
+__global__ __launch_bounds__(kSelThreads, 2) void select_wide_kernel(const T* __restrict__ lq,
+                                                                     const T* __restrict__ lk,
+                                                                     float* __restrict__ ls, int* __restrict__ lj,
+                                                                     SelParams p) {
+  constexpr int TILE = kS * kD;  // 64 rows of one 64-column chunk
+  __shared__ __attribute__((aligned(16))) T stage[2 * 4 * TILE];  // per stage: rows 0-63, 64-127, keys 0-63, 64-127
+  SelItem it;
+  if (!sel_item(p, it)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, l32 = lane & 31;
+  const int64_t r0 = it.r * kSelRows, t0w = r0 + 32 * wave;  // the block's and this wave's first row
+  const int64_t t = t0w + l32;                               // this lane's row
+  // rows and keys past the end repeat the last one (their scores are no candidates);
+  // a 64-row half that does not exist at all copies the one before it
+  auto half_of = [](int64_t first, int h, int64_t n) -> int64_t { return first + 64 * h < n ? first + 64 * h : first; };
+  const int64_t q0 = half_of(r0, 0, p.nQ), q1 = half_of(r0, 1, p.nQ);
+  const TileCopy<T, kSelWaves> cq0(wave, lane, p.D, (int)min<int64_t>(64, p.nQ - q0));
+  const TileCopy<T, kSelWaves> cq1(wave, lane, p.D, (int)min<int64_t>(64, p.nQ - q1));
+  const TileCopy<T, kSelWaves> cfull(wave, lane, p.D, 64);
+  const int64_t klast = (p.tiles - 1) * kWideTile;
+  const int64_t e0 = half_of(klast, 0, p.nKV), e1 = half_of(klast, 1, p.nKV);
+  const TileCopy<T, kSelWaves> ce0(wave, lane, p.D, (int)min<int64_t>(64, p.nKV - e0));
+  const TileCopy<T, kSelWaves> ce1(wave, lane, p.D, (int)min<int64_t>(64, p.nKV - e1));
+  const T* const qbase = lq + it.bhr * p.nQ * p.D;
+  const T* const kbase = lk + it.bhr * p.nKV * p.D;
+  constexpr int kLoads = 4 * TileCopy<T, kSelWaves>::kN;  // one wave's copies of one chunk
+  const int nch = p.D / kD;
+  auto tile_of = [&](int u) -> int64_t { return it.x + kSelClasses * (it.part * p.tpp + u); };
+  auto issue = [&](int u, int c, int st) __device__ {
+    T* dst = stage + st * 4 * TILE;
+    cq0.issue(qbase + q0 * p.D + c * kD, dst);
+    cq1.issue(qbase + q1 * p.D + c * kD, dst + TILE);
+    const int64_t j = tile_of(u);
+    if (j == p.tiles - 1) {
+      ce0.issue(kbase + e0 * p.D + c * kD, dst + 2 * TILE);
+      ce1.issue(kbase + e1 * p.D + c * kD, dst + 3 * TILE);
+    } else {
+      cfull.issue(kbase + j * kWideTile * p.D + c * kD, dst + 2 * TILE);
+      cfull.issue(kbase + (j * kWideTile + 64) * p.D + c * kD, dst + 3 * TILE);
+    }
+  };
+
+  TopKeys<KM> L;
+  L.init();
+  int st = 0;
+  issue(0, 0, 0);
+  for (int u = 0; u < it.nu; ++u) {
+    const int64_t j0 = tile_of(u) * kWideTile;  // first key chunk of the tile
+    // wave-uniform: some (row, key) pair of this wave's block is a candidate
+    const bool live = j0 < t0w + 31 && t0w < p.nQ;
+    f32x16 acc[kWideTile / 32];
 #pragma unroll
-  for (int e = 0; e < KM; ++e) {
-    uint32_t la, lb, ha, hb;
-    pair32((uint32_t)L.k[e], la, lb);
-    pair32((uint32_t)(L.k[e] >> 32), ha, hb);
-    const bool own_first = la == (uint32_t)L.k[e] && ha == (uint32_t)(L.k[e] >> 32);
-    pk[e] = own_first ? ((uint64_t)hb << 32 | lb) : ((uint64_t)ha << 32 | la);
-  }
-#pragma unroll
-  for (int e = 0; e < KM; ++e)
-    if (pk[e] != 0) L.insert(pk[e]);
-  if (hh == 0 && t < p.nQ) {
-    const int64_t o = ((bhr * p.nQ + t) * p.lists + x * p.parts_max + part) * p.K;
-#pragma unroll
-    for (int e = 0; e < KM; ++e) {
-      if (e < p.K) {
-        const bool real = L.k[e] != 0;
-        ls[o + e] = real ? key_score(L.k[e]) : -INFINITY;
-        lj[o + e] = real ? key_chunk(L.k[e]) : -1;
+    for (int b = 0; b < kWideTile / 32; ++b) acc[b] = zero16();
+    for (int c = 0; c < nch; ++c) {
+      const bool more = c + 1 < nch || u + 1 < it.nu;
+      if (more) {
+        if (c + 1 < nch) issue(u, c + 1, st ^ 1);
+        else issue(u + 1, 0, st ^ 1);
+        wait_vmem<kLoads>();
+      } else {
+        wait_vmem<0>();
       }
+      block_barrier();  // every wave's copies of this chunk are in
+      if (live) {
+        const T* sq = stage + st * 4 * TILE + (wave >> 1) * TILE;
+        const T* sk = stage + st * 4 * TILE + 2 * TILE;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+          const Frag<T> qf = lds_frag(sq, 32 * (wave & 1) + l32, 16 * kb + 8 * hh);
+#pragma unroll
+          for (int b = 0; b < kWideTile / 32; ++b)
+            mma32(acc[b], lds_frag(sk + (b >> 1) * TILE, 32 * (b & 1) + l32, 16 * kb + 8 * hh), qf);
+        }
+      }
+      block_barrier();  // the stage is free for the copy issued in the next step
+      st ^= 1;
+    }
+    if (live) {
+      uint32_t own;
+      const uint32_t pub = sel_publish(p, L, it.bhr, t, own);
+      const float ts = sel_threshold(own, pub);
+      const bool full = j0 + kWideTile <= t0w && j0 + kWideTile <= p.nKV && t0w + 31 < p.nQ;
+#pragma unroll
+      for (int b = 0; b < kWideTile / 32; ++b) sel_fold<KM, GUMBEL>(p, L, acc[b], j0 + 32 * b, it.bhr, t, ts, full);
     }
   }
+  sel_store(p, L, it, t, ls, lj);
 }
 
 __global__ void sel_clear_kernel(uint32_t* __restrict__ p, int64_t n) {
@@ -281,6 +411,7 @@ __global__ __launch_bounds__(256) void select_merge_kernel(const float* __restri
   }
 }
 
+// NCH: landmark chunks held in registers (select_part_kernel); 0: select_wide_kernel.
 template <typename T, int KM, bool GUMBEL, int NCH>
 hipError_t launch_split_select_n(const Shape& s, const void* lq, const void* lk, int32_t* idx, float* sel, void* ws,
                                hipStream_t st) {
@@ -295,6 +426,7 @@ hipError_t launch_split_select_n(const Shape& s, const void* lq, const void* lk,
   p.lists = plan.lists;
   p.D = s.D;
   p.K = s.topk;
+  p.tile = plan.tile;
   p.tpp = plan.tiles_per_part;
   p.tpp_shift = __builtin_ctz((unsigned)plan.tiles_per_part);
   p.scale = s.score_scale;
@@ -308,9 +440,14 @@ hipError_t launch_split_select_n(const Shape& s, const void* lq, const void* lk,
   launch_kernel("sel_clear_kernel", sel_clear_kernel, dim3((unsigned)std::min<int64_t>((nrows + 255) / 256, 1024)),
                 dim3(256), 0, st, p.gthr, nrows);
   const int64_t items = BHr * kSelClasses * plan.items_per_class;
-  if (items > 0)
-    launch_kernel("select_part_kernel", select_part_kernel<T, KM, GUMBEL, NCH>, dim3((unsigned)items),
-                  dim3(kSelThreads), 0, st, (const T*)lq, (const T*)lk, ls, lj, p);
+  if (items > 0) {
+    if constexpr (NCH > 0)
+      launch_kernel("select_part_kernel", select_part_kernel<T, KM, GUMBEL, NCH>, dim3((unsigned)items),
+                    dim3(kSelThreads), 0, st, (const T*)lq, (const T*)lk, ls, lj, p);
+    else
+      launch_kernel("select_wide_kernel", select_wide_kernel<T, KM, GUMBEL>, dim3((unsigned)items),
+                    dim3(kSelThreads), 0, st, (const T*)lq, (const T*)lk, ls, lj, p);
+  }
   const int64_t rows = BHr * s.nQ;
   launch_kernel("select_merge_kernel", select_merge_kernel<T, KM, GUMBEL>, dim3((unsigned)((rows + 3) / 4)),
                 dim3(256), 0, st, ls, lj, idx, sel, (const T*)lq, (const T*)lk, rows, p);
@@ -320,6 +457,7 @@ hipError_t launch_split_select_n(const Shape& s, const void* lq, const void* lk,
 template <typename T, int KM, bool GUMBEL>
 hipError_t launch_split_select(const Shape& s, const void* lq, const void* lk, int32_t* idx, float* sel, void* ws,
                                hipStream_t st) {
+  if (select_plan(s).tile == kWideTile) return launch_split_select_n<T, KM, GUMBEL, 0>(s, lq, lk, idx, sel, ws, st);
   switch (s.D / kD) {
     case 1: return launch_split_select_n<T, KM, GUMBEL, 1>(s, lq, lk, idx, sel, ws, st);
     case 2: return launch_split_select_n<T, KM, GUMBEL, 2>(s, lq, lk, idx, sel, ws, st);
@@ -343,7 +481,7 @@ hipError_t launch_split_select(const Shape& s, const void* lq, const void* lk, i
 
 hipError_t launch_fused_select(const Shape& s, const void* lmk_q, const void* lmk_k, int32_t* idx, float* sel,
                                void* ws, hipStream_t stream) {
-  if (!select_plan(s).split) return launch_fused_rowblocks(s, lmk_q, lmk_k, idx, sel, stream);
+  if (!select_plan(s).split || !ws) return launch_fused_rowblocks(s, lmk_q, lmk_k, idx, sel, stream);
   auto run = [&](auto tag, auto gumbel) {
     using T = decltype(tag);
     constexpr bool G = decltype(gumbel)::value;

@@ -68,3 +68,34 @@ def test_forward_wave_form_equals_pair_form(dev, B, H, Hr, nC, k, holes, obo):
     assert max_abs_rel(o0, o1) <= 2.0 ** -7    # two bf16 roundings of sums that differ in bf16 probabilities
     assert max_abs_rel(l0, l1) <= 1e-6
     assert max_abs_rel(w0, w1) <= 1e-6
+
+
+@pytest.mark.parametrize("dtype,D,nC,k,gumbel", [
+    ("bf16", 576, 1, 3, False),
+    ("bf16", 1024, 129, 8, False),       # two row blocks, the second of one row; a ragged second key tile
+    ("bf16", 640, 1100, 16, True),
+    ("bf16", 576, 9100, 5, False),       # several parts per class
+    ("fp32", 320, 700, 8, True),
+])
+def test_wide_select_equals_score_matrix(dev, dtype, D, nC, k, gumbel):
+    """Selection without the matrix for landmarks too wide for registers (its lists in the
+    output buffer), against the same selection from the score matrix and, with the output
+    in the query buffer, against the one-pass form that needs no scratch."""
+    import torch
+    from paper_2410_01651_amd import gca
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(D + nC)
+    lq, lk = (torch.randn(1, 2, nC, D, generator=g, device=dev, dtype=dt) for _ in range(2))
+    q, kk, v = (torch.randn(1, 2, nC * 64, 64, generator=g, device=dev, dtype=dt) for _ in range(3))
+    seed = 77 if gumbel else None
+    got = {}
+    for name, flags, out in (("split", gca.FLAG_FUSED_TOPK, None), ("matrix", gca.FLAG_MATERIALIZE, None),
+                             ("one pass", gca.FLAG_FUSED_TOPK, q)):
+        p = gca.problem(1, 2, nC, k, D=D, Hr=2, dtype=dtype, flags=flags, gumbel_seed=seed)
+        assert name == "matrix" or gca.workspace_size(p, gca.OP_FORWARD) == 0
+        f = gca.forward(p, lq, lk, q, kk, v, out=out)
+        got[name] = f["idx"].cpu().numpy(), host64(f["sel"])
+    for name in ("matrix", "one pass"):
+        # the scores are the same products summed in the same order
+        np.testing.assert_array_equal(got["split"][0], got[name][0])
+        assert max_abs_rel(got["split"][1], got[name][1]) <= 1e-5
