@@ -30,14 +30,12 @@ int device_cus() {
 // ----------------------------------------------------------- decode ----
 
 DecodePlan decode_plan(const Shape& s) {
-  // about 256 scan workgroups in all, every wave one contiguous range of at
-  // least 64 keys
+  // about 256 scan workgroups in all, every wave at least one group of 8 keys
   constexpr int64_t kWaves = 4;
   const int64_t rows = (int64_t)s.B * s.Hr;
   int64_t wgs = 256 / rows;
   if (wgs < 1) wgs = 1;
   int64_t pw = (s.nKV + wgs * kWaves - 1) / (wgs * kWaves);
-  if (pw < 64) pw = 64;
   pw = (pw + 7) & ~int64_t(7);
   DecodePlan p;
   p.pw = pw;
