@@ -99,3 +99,28 @@ def test_wide_select_equals_score_matrix(dev, dtype, D, nC, k, gumbel):
         # the scores are the same products summed in the same order
         np.testing.assert_array_equal(got["split"][0], got[name][0])
         assert max_abs_rel(got["split"][1], got[name][1]) <= 1e-5
+
+
+@pytest.mark.parametrize("B,H,nC,k,obo", [(65, 4, 40, 8, False), (20, 13, 9, 12, True), (130, 2, 33, 32, False),
+                                          (300, 1, 3, 5, False)])
+def test_decode_large_batch_equals_small(dev, B, H, nC, k, obo):
+    """Batches of more (batch, head) items than compute units keep one slot per wave pair
+    resident; the same items in batches of a few keep two."""
+    import torch
+    from paper_2410_01651_amd import gca
+    g = torch.Generator(device=dev).manual_seed(B)
+    D = 192
+    t = {n: torch.randn(s, generator=g, device=dev, dtype=torch.bfloat16)
+         for n, s in (("lmk_q", (B, 1, 1, D)), ("lmk_k", (B, 1, nC, D)), ("q", (B, H, 64, 64)),
+                      ("k", (B, H, nC * 64, 64)), ("v", (B, H, nC * 64, 64)))}
+    run = lambda b0, n: gca.forward(gca.problem(n, H, nC, k, D=D, mode="decode", off_by_one=obo),  # noqa: E731
+                                    *(t[x][b0:b0 + n].contiguous() for x in ("lmk_q", "lmk_k", "q", "k", "v")))
+    whole = run(0, B)
+    for b0 in range(0, B, 16):
+        part = run(b0, min(16, B - b0))
+        for n, tol in (("idx", 0.0), ("sel", 1e-6), ("w", 1e-6), ("lse", 1e-6), ("out", 2.0 ** -7)):
+            a, b = whole[n][b0:b0 + 16], part[n]
+            if n == "idx":
+                assert torch.equal(a, b)
+            else:
+                assert max_abs_rel(host64(a), host64(b)) <= tol, n
