@@ -83,8 +83,6 @@ struct BwdWs {
   float* Dbuf;     // [B*H, K, Lq]  -D_s per query token (slot-major: one slot's tokens contiguous; Lq = nQ * Sq)
   float* Lbuf;     // [B*H, K, Lq]  log2(e) lse - log2(w_s)
   float* dwp;      // [B*H, nQ, K, 2] dw partials per head and query half
-  int* counts;     // [B*Hr, nKV]
-  int* cursor;     // [B*Hr, nKV]
   int* offs;       // [B*Hr, nKV+1]
   int* unsorted;   // [B*Hr, nQ*K]
   int* sorted;     // [B*Hr, nQ*K]

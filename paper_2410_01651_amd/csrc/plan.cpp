@@ -136,8 +136,6 @@ BwdWs carve(const Shape& s, Carver& c) {
   w.Dbuf = c.take<float>(BH * s.nQ * s.Sq * s.topk);
   w.Lbuf = c.take<float>(BH * s.nQ * s.Sq * s.topk);
   w.dwp = c.take<float>(BH * s.nQ * s.topk * 2);
-  w.counts = c.take<int>(BHr * s.nKV);
-  w.cursor = c.take<int>(BHr * s.nKV);
   w.offs = c.take<int>(BHr * (s.nKV + 1));
   w.unsorted = c.take<int>(BHr * s.nQ * s.topk);
   w.sorted = c.take<int>(BHr * s.nQ * s.topk);

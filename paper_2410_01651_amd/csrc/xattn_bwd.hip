@@ -20,9 +20,8 @@
 //
 // No floating-point atomics: every output element is produced by exactly one
 // workgroup.  The key-stationary pass needs, for each chunk j, the list of
-// (row t, slot s) that retrieved it; an integer counting sort builds that list
-// (CSR) and a rank pass orders each list by (t, s), so the summation order, and
-// hence the result, is the same on every run.
+// (row t, slot s) that retrieved it, in (t, s) order (bwd_prep_kernel), so the
+// summation order, and hence the result, is the same on every run.
 #include "gca_device.hpp"
 #include "gca_launch.hpp"
 
@@ -69,118 +68,185 @@ struct LmkShared {
 
 // ------------------------------------------------------------ helpers ----
 
-__global__ void fill_zero_kernel(int* __restrict__ p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0;
+// ----------------------------------- fusion weights and inverse index ----
+
+// One launch prepares the backward.  Workgroup g of a (batch, retrieval head) slice
+//  - writes the fusion weights (Eq. 2, as the forward computed them) of the g-th `per`
+//    landmark rows;
+//  - builds the inverse index (CSR) of the g-th `per` key chunks: it reads the whole
+//    slice's retrieval lists, counts the entries of earlier chunks (the offset of its
+//    own lists) and collects its own.
+// An entry (t, s) is listed under chunk idx[t, s] when row t feeds a query chunk that
+// exists (causal: t + 1 < nQ).  Each list ends up ascending by (t, s): an entry's
+// position is the number of smaller entries in its list (entries are distinct), so the
+// order does not depend on the order of collection.
+//
+// Every workgroup reads all of its slice's lists (32 KiB at 1,024 chunks, from the L2)
+// instead of a count, a scan, a fill and a sort launch that each wait for the one
+// before: latency is all that bounds this step.  Six launches took 32 us at 64K tokens
+// (2 x 1,024 chunks, k = 8) and 23 us at 2K; this one takes 18 us and 7 us.
+constexpr int kPrepThreads = 256;
+constexpr int kPrepPool = 2048;   // entries collected in LDS; more go through global memory
+constexpr int kPrepMax = 1024;    // most chunks per workgroup
+// Chunks per workgroup: 16, since a causal slice's first chunks have the longest lists
+// (16 of them about 700 entries at 1,024 chunks and k = 8; 64 chunks per workgroup took
+// 46 us there), and more from 4,096 chunks up, so that at most 256 workgroups read
+// each slice (1,024 from 262,144 up).
+inline int prep_chunks(int64_t nKV) {
+  int per = 16;
+  while (per < kPrepMax && nKV > (int64_t)per * 256) per *= 4;
+  return per;
 }
-
-// Fusion weights of every retrieval row (Eq. 2), as the forward computed them.
-__global__ void weights_kernel(const int32_t* __restrict__ idx, const float* __restrict__ sel,
-                               float* __restrict__ w, int64_t rows, int K, int64_t nKV) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= rows * K) return;
-  const int64_t row = e / K;
-  const int s = (int)(e % K);
-  float wv;
-  int jv;
-  row_weight(idx + row * K, sel + row * K, K, nKV, s, wv, jv);
-  w[e] = wv;
-}
-
-// ----------------------------------------------------- inverse index ----
-
-// An entry (t, s) is listed under chunk idx[t, s] when row t feeds a query
-// chunk that exists (causal: t + 1 < nQ; decode: t == 0).
-__device__ __forceinline__ bool entry_live(int64_t t, int64_t nQ, int causal) {
-  return t + causal < nQ;
-}
-
-__global__ void csr_count_kernel(const int32_t* __restrict__ idx, int* __restrict__ counts, int64_t BHr,
-                                 int64_t nQ, int K, int64_t nKV, int causal) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= BHr * nQ * K) return;
-  const int64_t bhr = e / (nQ * K);
-  const int64_t t = (e / K) % nQ;
-  const int j = idx[e];
-  if (j >= 0 && j < nKV && entry_live(t, nQ, causal)) atomicAdd(&counts[bhr * nKV + j], 1);
-}
-
-// Exclusive scan of one (b, hr) count row: offs[0..nKV], cursor = offs[0..nKV).
-__global__ __launch_bounds__(1024) void csr_scan_kernel(const int* __restrict__ counts, int* __restrict__ offs,
-                                                        int* __restrict__ cursor, int64_t nKV) {
-  __shared__ int sWave[16];
-  __shared__ int sCarry;
-  const int64_t bhr = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int* cnt = counts + bhr * nKV;
-  int* off = offs + bhr * (nKV + 1);
-  int* cur = cursor + bhr * nKV;
-  if (tid == 0) sCarry = 0;
-  __syncthreads();
-  for (int64_t base = 0; base < nKV; base += 1024) {
-    const int64_t i = base + tid;
-    const int v = i < nKV ? cnt[i] : 0;
-    int x = v;  // inclusive scan within the wave
+// Position of e in an ascending order of list[lo .. hi): the smaller entries.
+__device__ __forceinline__ int prep_rank(const int* list, int lo, int hi, int e) {
+  int rank = 0, u = lo;
+  for (; u + 8 <= hi; u += 8) {
+    int v[8];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    if (lane == 63) sWave[wave] = x;
-    __syncthreads();
-    int before = sCarry;
-    for (int w = 0; w < wave; ++w) before += sWave[w];
-    const int excl = before + x - v;
-    if (i < nKV) {
-      off[i] = excl;
-      cur[i] = excl;
-    }
-    __syncthreads();
-    if (tid == 1023) sCarry = excl + v;
-    __syncthreads();
+    for (int i = 0; i < 8; ++i) v[i] = list[u + i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) rank += v[i] < e ? 1 : 0;
   }
-  if (tid == 0) off[nKV] = sCarry;
+  for (; u < hi; ++u) rank += list[u] < e ? 1 : 0;
+  return rank;
 }
-
-__global__ void csr_fill_kernel(const int32_t* __restrict__ idx, int* __restrict__ cursor,
-                                int* __restrict__ unsorted, int64_t BHr, int64_t nQ, int K, int64_t nKV,
-                                int causal) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= BHr * nQ * K) return;
-  const int64_t bhr = e / (nQ * K);
-  const int64_t local = e % (nQ * K);  // t * K + s
-  const int64_t t = local / K;
-  const int j = idx[e];
-  if (j >= 0 && j < nKV && entry_live(t, nQ, causal)) {
-    const int pos = atomicAdd(&cursor[bhr * nKV + j], 1);
-    unsorted[bhr * nQ * K + pos] = (int)local;
+__global__ __launch_bounds__(kPrepThreads) void bwd_prep_kernel(const int32_t* __restrict__ idx,
+                                                                const float* __restrict__ sel, BwdWs ws,
+                                                                int64_t nQ, int K, int64_t nKV, int causal,
+                                                                int per, int64_t groups) {
+  __shared__ int sE[kPrepPool];             // collected entries ...
+  __shared__ unsigned short sJ[kPrepPool];  // ... and their chunks (less the group's first)
+  __shared__ int sList[kPrepPool];          // the same grouped by chunk
+  __shared__ int sCnt[kPrepMax], sCur[kPrepMax], sOff[kPrepMax + 1];
+  __shared__ int sBelow, sM;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t bhr = blockIdx.x / groups, g = blockIdx.x % groups;
+  const int64_t j0 = g * per;
+  const int nj = (int)min<int64_t>(per, nKV - j0);
+  const int32_t* lists = idx + bhr * nQ * K;
+  const int n = (int)((nQ - causal) * K);  // entries of rows that feed a chunk: a prefix
+  for (int i = tid; i < (per + 63 & ~63); i += kPrepThreads) {
+    sCnt[i] = 0;
+    sCur[i] = 0;
   }
-}
-
-// Order each chunk's list ascending by (t, s): an entry's position is the number
-// of smaller entries in its list (entries are distinct).  One wave per chunk.
-__global__ __launch_bounds__(256) void csr_sort_kernel(const int* __restrict__ offs, const int* __restrict__ unsorted,
-                                                       int* __restrict__ sorted, int* __restrict__ head, int64_t BHr,
-                                                       int64_t nQ, int K, int64_t nKV) {
-  const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wv >= BHr * nKV) return;
-  const int lane = threadIdx.x & 63;
-  const int64_t bhr = wv / nKV, j = wv % nKV;
-  const int* off = offs + bhr * (nKV + 1);
-  const int lo = off[j], hi = off[j + 1];
-  const int* src = unsorted + bhr * nQ * K;
-  int* dst = sorted + bhr * nQ * K;
-  int* hd = head + wv * kHeadInts;
-  if (lane == 0) {
-    hd[0] = lo;
-    hd[1] = hi - lo;
+  if (tid == 0) {
+    sBelow = 0;
+    sM = 0;
   }
-  for (int i = lo + lane; i < hi; i += 64) {
-    const int e = src[i];
-    int rank = 0;
-    for (int u = lo; u < hi; ++u) rank += src[u] < e ? 1 : 0;
-    dst[lo + rank] = e;
-    if (rank < kHeadEntries) hd[2 + rank] = e;
+  __syncthreads();
+
+  constexpr int kB = 16;  // loads in flight per thread
+  int below = 0;
+  for (int64_t e0 = 0; e0 < n; e0 += kPrepThreads * kB) {
+    int j[kB];
+#pragma unroll
+    for (int m = 0; m < kB; ++m) {
+      const int64_t e = e0 + m * kPrepThreads + tid;
+      j[m] = e < n ? lists[e] : -1;
+    }
+#pragma unroll
+    for (int m = 0; m < kB; ++m) {
+      const bool valid = j[m] >= 0 && j[m] < nKV;
+      const int64_t d = j[m] - j0;
+      below += valid && d < 0 ? 1 : 0;
+      const bool mine = valid && d >= 0 && d < per;
+      const uint64_t mask = __ballot(mine);
+      if (mask == 0) continue;  // one reservation per wave
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&sM, __popcll(mask));
+      at = __builtin_amdgcn_readfirstlane(at) + lanes_below(mask);
+      if (mine) {
+        atomicAdd(&sCnt[d], 1);
+        if (at < kPrepPool) {
+          sE[at] = (int)(e0 + m * kPrepThreads + tid);
+          sJ[at] = (unsigned short)d;
+        }
+      }
+    }
+  }
+  // (a slice has fewer than 2^31 entries)
+  for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
+  if (lane == 0) atomicAdd(&sBelow, below);
+  __syncthreads();
+  if (wave == 0) {  // exclusive scan of the counts
+    int carry = 0;
+    for (int i0 = 0; i0 < per; i0 += 64) {
+      const int v = sCnt[i0 + lane];
+      int x = v;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+      }
+      sOff[i0 + lane] = carry + x - v;
+      carry += __shfl(x, 63);
+    }
+    if (lane == 0) sOff[per] = carry;
+  }
+  __syncthreads();
+  const int base = sBelow, m = sM;
+  int* offs = ws.offs + bhr * (nKV + 1);
+  int* sorted = ws.sorted + bhr * nQ * K;
+  int* head = ws.head + (bhr * nKV + j0) * kHeadInts;
+  for (int d = tid; d < nj; d += kPrepThreads) {
+    offs[j0 + d] = base + sOff[d];
+    head[d * kHeadInts] = base + sOff[d];
+    head[d * kHeadInts + 1] = sCnt[d];
+  }
+  if (tid == 0 && g == groups - 1) offs[nKV] = base + m;
+
+  if (m <= kPrepPool) {
+    for (int i = tid; i < m; i += kPrepThreads) {
+      const int d = sJ[i];
+      sList[sOff[d] + atomicAdd(&sCur[d], 1)] = sE[i];
+    }
+    __syncthreads();
+    for (int i = tid; i < m; i += kPrepThreads) {
+      const int d = sJ[i], e = sE[i], lo = sOff[d], hi = sOff[d + 1];
+      const int rank = prep_rank(sList, lo, hi, e);
+      sorted[base + lo + rank] = e;
+      if (rank < kHeadEntries) head[d * kHeadInts + 2 + rank] = e;
+    }
+  } else {
+    int* list = ws.unsorted + bhr * nQ * K + base;
+    for (int64_t e = tid; e < n; e += kPrepThreads) {
+      const int j = lists[e];
+      if (j < 0 || j >= nKV) continue;
+      const int64_t d = j - j0;
+      if (d >= 0 && d < per) list[sOff[d] + atomicAdd(&sCur[d], 1)] = (int)e;
+    }
+    __syncthreads();  // the workgroup's own global writes are visible to it
+    for (int d = wave; d < nj; d += kPrepThreads / 64) {
+      const int lo = sOff[d], hi = sOff[d + 1];
+      for (int i = lo + lane; i < hi; i += 64) {
+        const int e = list[i];
+        const int rank = prep_rank(list, lo, hi, e);
+        sorted[base + lo + rank] = e;
+        if (rank < kHeadEntries) head[d * kHeadInts + 2 + rank] = e;
+      }
+    }
+  }
+
+  // fusion weights: the rows' chunks and scores through LDS (the pool's space, read
+  // above) a few rows at a time, then one (row, slot) per thread
+  const int64_t r1 = min<int64_t>((g + 1) * per, nQ);
+  const int rows = kPrepPool / K;
+  for (int64_t r0 = g * per; r0 < r1; r0 += rows) {
+    const int64_t at0 = (bhr * nQ + r0) * K;
+    const int ne = (int)min<int64_t>(rows, r1 - r0) * K;
+    __syncthreads();
+    for (int e = tid; e < ne; e += kPrepThreads) {
+      sE[e] = idx[at0 + e];
+      sList[e] = __float_as_int(sel[at0 + e]);
+    }
+    __syncthreads();
+    for (int e = tid; e < ne; e += kPrepThreads) {
+      const int row = e / K * K;
+      float wv;
+      int jv;
+      row_weight(sE + row, reinterpret_cast<const float*>(sList) + row, K, nKV, e - row, wv, jv);
+      ws.w[at0 + e] = wv;
+    }
   }
 }
 
@@ -995,13 +1061,13 @@ __global__ __launch_bounds__(64) void dsel_kernel(const float* __restrict__ w, c
   if (s < K) dsel[row * K + s] = ws * (dw - tot);
 }
 
-// Weighted sum of gathered landmark rows by one 256-thread workgroup:
+// Weighted sum of gathered landmark rows by one workgroup:
 //   out[x] = scale * sum_u w_u src[row_u][x],  x < D,
 // for the n (row, weight) pairs staged in sRow / sW.  A thread owns a 16-byte
 // column block and a residue class of u (the groups), so every load is an
 // independent 16-byte read and four are in flight; the groups' partial sums are
 // added in a fixed order (deterministic).
-constexpr int kMaxGatherPasses = 8;  // D <= 8192: at most 8 passes of 256 blocks (fp32)
+constexpr int kMaxGatherPasses = 8;  // D <= 8192: at most 8 passes of 256 blocks (fp32); one pass of 64 threads
 
 template <typename T>
 __device__ __forceinline__ float elem16(const u32x4& r, int m) {
@@ -1070,15 +1136,19 @@ __device__ __forceinline__ void gather_store(float* __restrict__ out, int D, flo
   }
 }
 
-// column blocks per pass and retriever groups for a 256-thread workgroup
+// Threads per workgroup, column blocks per pass and retriever groups.  One wave where
+// it covers a row: both kernels are a chain of dependent reads per row, so what counts
+// is the rows in flight (16 heads x 700 rows of width 64, k = 16, in workgroups of 256:
+// 46 us for dlmk_q and 51 us for dlmk_k; of 64: 16 us and 19 us).
 struct GatherShape {
-  int pass_cols, groups;
+  int threads, pass_cols, groups;
 };
 inline GatherShape gather_shape(int D, int elem_bytes) {
   const int nb = D / (16 / elem_bytes);
   GatherShape g;
-  g.pass_cols = nb < 256 ? nb : 256;
-  g.groups = 256 / g.pass_cols;
+  g.threads = nb <= 64 ? 64 : 256;
+  g.pass_cols = nb < g.threads ? nb : g.threads;
+  g.groups = g.threads / g.pass_cols;
   return g;
 }
 
@@ -1087,8 +1157,8 @@ inline GatherShape gather_shape(int D, int elem_bytes) {
 // formed here and written out, so the backward needs no separate dsel launch
 // when the landmark-query gradient is wanted: all 256 threads read the head
 // classes of the dw partials, and the first wave forms dsel.
-template <typename T>
-__global__ __launch_bounds__(256) void dlmk_q_kernel(const T* __restrict__ lk, const int32_t* __restrict__ idx,
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void dlmk_q_kernel(const T* __restrict__ lk, const int32_t* __restrict__ idx,
                                                      const float* __restrict__ w, const float* __restrict__ dwp,
                                                      float* __restrict__ dsel, float* __restrict__ dlq,
                                                      int64_t nQ, int64_t nKV, int D, int K, int H, int Hr,
@@ -1097,7 +1167,7 @@ __global__ __launch_bounds__(256) void dlmk_q_kernel(const T* __restrict__ lk, c
   __shared__ int64_t sRow[32];
   __shared__ float sW[32];
   __shared__ int sN;
-  __shared__ float sAcc[256 * 8];
+  __shared__ float sAcc[NT * 8];
   __shared__ float sCls[kDwClasses][32];
   const int64_t row = blockIdx.x;
   const int64_t bhr = row / nQ;
@@ -1105,10 +1175,12 @@ __global__ __launch_bounds__(256) void dlmk_q_kernel(const T* __restrict__ lk, c
   const int64_t b = bhr / Hr;
   const int hr = (int)(bhr % Hr);
   {
-    // the dw partials of every head are read by all 256 threads at once: thread
+    // the dw partials of every head are read by all threads at once: thread
     // (class c, slot s) sums head class c of slot s
-    const int s = threadIdx.x & 31, c = threadIdx.x >> 5;
-    sCls[c][s] = (s < K && t + causal < nQ) ? dw_class(dwp, b, t, s, H, Hr, hr, nQ, K, c) : 0.f;
+    const int s = threadIdx.x & 31;
+#pragma unroll
+    for (int c = threadIdx.x >> 5; c < kDwClasses; c += NT / 32)
+      sCls[c][s] = (s < K && t + causal < nQ) ? dw_class(dwp, b, t, s, H, Hr, hr, nQ, K, c) : 0.f;
   }
   __syncthreads();
   if (threadIdx.x < 64) {
@@ -1141,8 +1213,8 @@ __global__ __launch_bounds__(256) void dlmk_q_kernel(const T* __restrict__ lk, c
 
 // dlmk_k[j] = score_scale * sum over the rows (t, s) that retrieved j of dsel[t, s] lmk_q[t],
 // in (t, s) order within each group of the list
-template <typename T>
-__global__ __launch_bounds__(256) void dlmk_k_kernel(const T* __restrict__ lq, const int* __restrict__ offs,
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void dlmk_k_kernel(const T* __restrict__ lq, const int* __restrict__ offs,
                                                      const int* __restrict__ sorted, const float* __restrict__ dsel,
                                                      float* __restrict__ dlk, int64_t nQ, int64_t nKV, int D, int K,
                                                      float scale, GatherShape gs) {
@@ -1150,7 +1222,7 @@ __global__ __launch_bounds__(256) void dlmk_k_kernel(const T* __restrict__ lq, c
   constexpr int NB = 256;
   __shared__ int64_t sRow[NB];
   __shared__ float sW[NB];
-  __shared__ float sAcc[256 * 8];
+  __shared__ float sAcc[NT * 8];
   const int64_t wid = blockIdx.x;  // (b, hr, j)
   const int64_t bhr = wid / nKV, j = wid % nKV;
   const int* off = offs + bhr * (nKV + 1);
@@ -1162,10 +1234,10 @@ __global__ __launch_bounds__(256) void dlmk_k_kernel(const T* __restrict__ lq, c
   for (int b0 = lo; b0 < hi; b0 += NB) {
     const int nb = min(NB, hi - b0);
     __syncthreads();
-    if (threadIdx.x < nb) {
-      const int e = list[b0 + threadIdx.x];  // t * K + s
-      sRow[threadIdx.x] = bhr * nQ + e / K;
-      sW[threadIdx.x] = dsel[(bhr * nQ) * K + e];
+    for (int i = threadIdx.x; i < nb; i += NT) {
+      const int e = list[b0 + i];  // t * K + s
+      sRow[i] = bhr * nQ + e / K;
+      sW[i] = dsel[(bhr * nQ) * K + e];
     }
     __syncthreads();
     gather_rows<T>(lq, D, sRow, sW, nb, acc, gs.pass_cols, gs.groups);
@@ -1173,26 +1245,16 @@ __global__ __launch_bounds__(256) void dlmk_k_kernel(const T* __restrict__ lq, c
   gather_store<T>(dlk + wid * D, D, scale, sAcc, acc, gs.pass_cols, gs.groups);
 }
 
-inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
-
 template <typename T>
 hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* lmk_q, const void* lmk_k,
                         float* dlmk_q, float* dlmk_k, hipStream_t st) {
   const int64_t BHr = (int64_t)s.B * s.Hr, BH = (int64_t)s.B * s.H;
-  const int64_t nent = BHr * s.nQ * s.topk;
   BwdWs& w = p.ws;
-  launch_kernel("weights_kernel", weights_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, p.idx, p.sel, w.w,
-                BHr * s.nQ, s.topk, s.nKV);
-  const unsigned zblocks = std::min(blocks_for(BHr * s.nKV, 256), 4096u);
-  launch_kernel("fill_zero_kernel", fill_zero_kernel, dim3(zblocks), dim3(256), 0, st, w.counts, BHr * s.nKV);
-  launch_kernel("csr_count_kernel", csr_count_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, p.idx, w.counts,
-                BHr, s.nQ, s.topk, s.nKV, s.causal);
-  launch_kernel("csr_scan_kernel", csr_scan_kernel, dim3((unsigned)BHr), dim3(1024), 0, st, w.counts, w.offs,
-                w.cursor, s.nKV);
-  launch_kernel("csr_fill_kernel", csr_fill_kernel, dim3(blocks_for(nent, 256)), dim3(256), 0, st, p.idx, w.cursor,
-                w.unsorted, BHr, s.nQ, s.topk, s.nKV, s.causal);
-  launch_kernel("csr_sort_kernel", csr_sort_kernel, dim3(blocks_for(BHr * s.nKV, 4)), dim3(256), 0, st, w.offs,
-                w.unsorted, w.sorted, w.head, BHr, s.nQ, s.topk, s.nKV);
+  // (decode has one landmark row: the groups of its past cover it too)
+  const int per = prep_chunks(s.nKV);
+  const int64_t groups = (s.nKV + per - 1) / per;
+  launch_kernel("bwd_prep_kernel", bwd_prep_kernel, dim3((unsigned)(BHr * groups)), dim3(kPrepThreads), 0, st, p.idx,
+                p.sel, w, s.nQ, s.topk, s.nKV, s.causal, per, groups);
   const int64_t nq_work = BH * s.nQ, nk_work = BH * s.nKV;
   // persistent: kWgPerCu workgroups per CU, kPairs chunk streams each
   const int64_t dq_wgs =
@@ -1209,19 +1271,20 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
     launch_kernel("bwd_dkdv_kernel", kernel, dim3((unsigned)round8(nk_work)), dim3(kKvThreads), 0, st, p, nk_work);
   };
   xr ? kv(bwd_dkdv_kernel<T, true>) : kv(bwd_dkdv_kernel<T, false>);
+  const GatherShape gs = gather_shape(s.D, sizeof(T));
   if (dlmk_q) {
     // dsel is formed inside the landmark-query gradient kernel
-    launch_kernel("dlmk_q_kernel", dlmk_q_kernel<T>, dim3((unsigned)(BHr * s.nQ)), dim3(256), 0, st, (const T*)lmk_k,
-                  p.idx, w.w, w.dwp, dsel, dlmk_q, s.nQ, s.nKV, s.D, s.topk, s.H, s.Hr, s.causal, s.score_scale,
-                  gather_shape(s.D, sizeof(T)));
+    launch_kernel("dlmk_q_kernel", gs.threads == 64 ? dlmk_q_kernel<T, 64> : dlmk_q_kernel<T, 256>,
+                  dim3((unsigned)(BHr * s.nQ)), dim3(gs.threads), 0, st, (const T*)lmk_k, p.idx, w.w, w.dwp, dsel,
+                  dlmk_q, s.nQ, s.nKV, s.D, s.topk, s.H, s.Hr, s.causal, s.score_scale, gs);
   } else {
     launch_kernel("dsel_kernel", dsel_kernel, dim3((unsigned)(BHr * s.nQ)), dim3(64), 0, st, w.w, w.dwp, dsel,
                   s.nQ, s.H, s.Hr, s.topk, s.causal);
   }
   if (dlmk_k) {
-    launch_kernel("dlmk_k_kernel", dlmk_k_kernel<T>, dim3((unsigned)(BHr * s.nKV)), dim3(256), 0, st, (const T*)lmk_q,
-                  w.offs, w.sorted, dsel, dlmk_k, s.nQ, s.nKV, s.D, s.topk, s.score_scale,
-                  gather_shape(s.D, sizeof(T)));
+    launch_kernel("dlmk_k_kernel", gs.threads == 64 ? dlmk_k_kernel<T, 64> : dlmk_k_kernel<T, 256>,
+                  dim3((unsigned)(BHr * s.nKV)), dim3(gs.threads), 0, st, (const T*)lmk_q, w.offs, w.sorted, dsel,
+                  dlmk_k, s.nQ, s.nKV, s.D, s.topk, s.score_scale, gs);
   }
   return take_launch_error();
 }

@@ -124,3 +124,66 @@ def test_decode_large_batch_equals_small(dev, B, H, nC, k, obo):
                 assert torch.equal(a, b)
             else:
                 assert max_abs_rel(host64(a), host64(b)) <= tol, n
+
+
+@pytest.mark.parametrize("mode,Hr,nC,k,D,hot", [
+    ("causal", 1, 2, 1, 64, False),
+    ("causal", 1, 17, 3, 64, False),       # a second group of one chunk
+    ("causal", 2, 300, 8, 512, True),      # one group collects more entries than fit in LDS
+    ("causal", 1, 4200, 2, 1024, False),   # 64 chunks per group; landmark rows of two waves
+    ("decode", 1, 70000, 9, 192, False),   # 1,024 chunks per group, one landmark row
+])
+def test_backward_preparation(dev, mode, Hr, nC, k, D, hot):
+    """Fusion weights, inverse lists and landmark gradients against fp64 torch: with dV and
+    the landmark gradients linear in them, a missing, doubled or misplaced list entry is
+    an error of the size of the result (tolerance: the bf16 rounding of dV, fp32 sums)."""
+    import torch
+    from paper_2410_01651_amd import gca
+    B, H = 1, 2
+    nQ = nC if mode == "causal" else 1
+    rng = np.random.default_rng(nC)
+    idx = np.full((B, Hr, nQ, k), -1, np.int32)
+    sel = np.full((B, Hr, nQ, k), -np.inf, np.float32)
+    for r in range(Hr):
+        for t in range(nQ):
+            past = t if mode == "causal" else nC
+            n = min(past, k)
+            idx[0, r, t, :n] = np.arange(n) if hot else np.sort(rng.choice(past, size=n, replace=False))
+            sel[0, r, t, :n] = rng.standard_normal(n)
+    ti, ts = torch.from_numpy(idx).to(dev), torch.from_numpy(sel).to(dev)
+    g = torch.Generator(device=dev).manual_seed(nC)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=dev, dtype=torch.bfloat16)  # noqa: E731
+    q, do = rnd(B, H, nQ * 64, 64), rnd(B, H, nQ * 64, 64)
+    kk, v = rnd(B, H, nC * 64, 64), rnd(B, H, nC * 64, 64)
+    lq, lk = rnd(B, Hr, nQ, D), rnd(B, Hr, nC, D)
+    p = gca.problem(B, H, nC, k, D=D, Hr=Hr, mode=mode)
+    _, lse, w = gca.grouped_xattn_fwd(p, q, kk, v, ti, ts)
+    d = gca.grouped_xattn_bwd(p, q, kk, v, ti, ts, lse, do, lq, lk)
+    w64 = torch.softmax(ts.double(), dim=-1).nan_to_num(0.0)
+    dv = torch.zeros(H, nC, 64, 64, dtype=torch.float64, device=dev)
+    shift = 1 if mode == "causal" else 0
+    for h in range(H):
+        r = h if Hr > 1 else 0
+        for s in range(k):
+            j = ti[0, r, :nQ - shift, s].long()
+            t = torch.nonzero(j >= 0)[:, 0]
+            if not len(t):
+                continue
+            j, c = j[t], t + shift
+            a = torch.bmm(q[0, h].view(nQ, 64, 64)[c].double(),
+                          kk[0, h].view(nC, 64, 64)[j].double().transpose(1, 2).contiguous()) / 8
+            pw = torch.softmax(a, dim=2) * w64[0, r, t, s][:, None, None]
+            dv[h].index_add_(0, j, torch.bmm(pw.transpose(1, 2).contiguous(), do[0, h].view(nQ, 64, 64)[c].double()))
+    assert max_abs_rel(host64(d["dv"]), dv.view(1, H, nC * 64, 64).cpu().numpy()) <= 2.0 ** -7
+    # landmark gradients from the kernel's own dsel
+    glq, glk = torch.zeros(Hr, nQ, D, dtype=torch.float64, device=dev), torch.zeros(Hr, nC, D, dtype=torch.float64,
+                                                                                    device=dev)
+    for r in range(Hr):
+        for s in range(k):
+            j = ti[0, r, :, s].long()
+            t = torch.nonzero(j >= 0)[:, 0]
+            c = d["dsel"][0, r, t, s].double()[:, None] / D ** 0.5
+            glq[r, t] += c * lk[0, r, j[t]].double()
+            glk[r].index_add_(0, j[t], c * lq[0, r, t].double())
+    assert max_abs_rel(host64(d["dlmk_q"]), glq[None].cpu().numpy()) <= 1e-5
+    assert max_abs_rel(host64(d["dlmk_k"]), glk[None].cpu().numpy()) <= 1e-5
