@@ -685,6 +685,208 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void bwd_dq_kernel(BwdParams p,
   }
 }
 
+// The same pass for few query chunks (few_pairs): one workgroup of several wave pairs per
+// chunk, the pairs taking its slots side by side (two resident slots per pair in bf16,
+// one in fp32) and adding their dQ through LDS in pair order, instead of one pair taking
+// them one after another on a chip that is mostly idle.
+template <typename T, int PAIRS>
+__global__ __launch_bounds__(128 * PAIRS, PAIRS == 4 ? 1 : 2) void bwd_dq_few_kernel(BwdParams p) {
+  constexpr int TILE = kS * kD;
+  constexpr bool kB16 = std::is_same<T, __bf16>::value;
+  constexpr int SP = kB16 ? 2 : 1;  // resident slots per pair
+  constexpr int kPerRound = PAIRS * SP;
+  constexpr uint32_t kTileB = TILE * sizeof(T), kRowB = kD * sizeof(T);
+  __shared__ __attribute__((aligned(16))) T ring[PAIRS * SP * 2 * TILE];  // K and V tiles; then the partial dQ
+  __shared__ int sSlot[32], sJc[32];
+  __shared__ float sWc[32];
+  __shared__ int sN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, l32 = lane & 31;
+  const int pair = wave >> 1, half = wave & 1;
+  const int64_t wi = blockIdx.x;  // (batch, head, query chunk)
+  const int64_t bh = wi / p.nQ, c = wi % p.nQ;
+  const int64_t b = bh / p.H;
+  const int h = (int)(bh % p.H);
+  const int K = p.K;
+  const bool has_row = !p.causal || c > 0;
+  const int64_t t = p.causal && has_row ? c - 1 : c;
+  const int64_t ro = ((b * p.Hr + (p.Hr == 1 ? 0 : h)) * p.nQ + t) * K;
+  const int64_t tglob = bh * p.nQ + t;  // dw row (b, h, t)
+  const int qi = 32 * half + l32;
+  const int64_t tok0 = wi * kS, lq_len = p.nQ * kS;
+  const int64_t cbase = bh * K * lq_len + c * kS;
+  const float sc = p.attn_scale * kLog2e;
+  const int cb = 16 * ((lane >> 4) & 1);
+
+  Frag<T> qf[4], df[4];
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb) {
+    qf[kb] = load_frag(reinterpret_cast<const T*>(p.q) + (tok0 + qi) * kD + 16 * kb + 8 * hh);
+    df[kb] = load_frag(reinterpret_cast<const T*>(p.dout) + (tok0 + qi) * kD + 16 * kb + 8 * hh);
+  }
+  if (wave == 0) {
+    int j = -1;
+    float w = 0.f;
+    if (has_row && lane < K) {
+      j = p.idx[ro + lane];
+      w = p.ws.w[ro + lane];
+    }
+    const bool valid = j >= 0 && j < p.nKV;
+    const uint64_t mask = __ballot(valid);
+    if (valid) {
+      const int rk = lanes_below(mask);
+      sSlot[rk] = lane;
+      sJc[rk] = j;
+      sWc[rk] = w;
+    } else if (has_row && lane < K) {
+      // a slot without a chunk: zero dw partials
+      p.ws.dwp[(tglob * K + lane) * 2] = 0.f;
+      p.ws.dwp[(tglob * K + lane) * 2 + 1] = 0.f;
+    }
+    if (lane == 0) sN = __popcll(mask);
+  }
+  __syncthreads();
+  const int n = sN;
+  const TileCopy<T, 2> cp(half, lane);
+  const T* const gk = reinterpret_cast<const T*>(p.k) + bh * p.nKV * TILE;
+  const T* const gv = reinterpret_cast<const T*>(p.v) + bh * p.nKV * TILE;
+  const lds_char* const lds0 = (const lds_char*)(ring);
+  uint32_t kofs[4], tofs[2][2];
+  {
+    const uint32_t pb = (uint32_t)pair * SP * 2 * kTileB;
+    const int s16 = lane & 15;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) kofs[kb] = pb + Swz<T>::off(l32, 16 * kb + 8 * hh) * sizeof(T);
+#pragma unroll
+    for (int dh = 0; dh < 2; ++dh)
+#pragma unroll
+      for (int r8 = 0; r8 < 2; ++r8)
+        tofs[dh][r8] = pb + Swz<T>::off(8 * r8 + 4 * hh + (s16 >> 2), 32 * dh + cb + 4 * (s16 & 3)) * sizeof(T);
+  }
+  f32x16 g0 = zero16(), g1 = zero16();  // dQ^T, d rows 0-31 / 32-63
+  auto run = [&](int slot, int i, float lse_q) __device__ {
+    const int s = sSlot[i];
+    const float ws = sWc[i];
+    const uint32_t co = (uint32_t)slot * 2 * kTileB;
+    const T* sK = ring + (pair * SP + slot) * (2 * TILE);
+    const T* sV = sK + TILE;
+    auto row = [&](int kb, int half32, bool v) __device__ -> Frag<T> {
+      if constexpr (kB16)
+        return lds_b128_at(lds0 + (kofs[kb] + co) + (v ? kTileB : 0u) + half32 * 32 * kRowB);
+      else
+        return lds_frag(v ? sV : sK, 32 * half32 + l32, 16 * kb + 8 * hh);
+    };
+    f32x16 s0 = zero16(), s1 = zero16(), p0 = zero16(), p1 = zero16();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      mma32(s0, row(kb, 0, false), qf[kb]);
+      mma32(s1, row(kb, 1, false), qf[kb]);
+      mma32(p0, row(kb, 0, true), df[kb]);
+      mma32(p1, row(kb, 1, true), df[kb]);
+    }
+    // as in bwd_dq_kernel
+    const float wsf = fmaxf(ws, 1e-30f);
+    const float off = lse_q * kLog2e - __builtin_amdgcn_logf(wsf);
+    float Dw = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s0[e] = __builtin_amdgcn_exp2f(fmaf(s0[e], sc, -off));
+      s1[e] = __builtin_amdgcn_exp2f(fmaf(s1[e], sc, -off));
+      Dw = fmaf(s0[e], p0[e], Dw);
+      Dw = fmaf(s1[e], p1[e], Dw);
+    }
+    const float Dq = sum_xor32(Dw) * __builtin_amdgcn_rcpf(wsf);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      s0[e] = s0[e] * (p0[e] - Dq);
+      s1[e] = s1[e] * (p1[e] - Dq);
+    }
+    Frag<T> f[4];
+    frag_from_acc(f[0], s0, 0, 1.f);
+    frag_from_acc(f[1], s0, 1, 1.f);
+    frag_from_acc(f[2], s1, 0, 1.f);
+    frag_from_acc(f[3], s1, 1, 1.f);
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      if constexpr (kB16) {
+        mma32(g0, lds_tr2(lds0 + (tofs[0][0] + co) + 16 * kb * kRowB, lds0 + (tofs[0][1] + co) + 16 * kb * kRowB), f[kb]);
+        mma32(g1, lds_tr2(lds0 + (tofs[1][0] + co) + 16 * kb * kRowB, lds0 + (tofs[1][1] + co) + 16 * kb * kRowB), f[kb]);
+      } else {
+        mma32(g0, lds_frag_t(sK, 16 * kb + 4 * hh, 16 * kb + 8 + 4 * hh, cb), f[kb]);
+        mma32(g1, lds_frag_t(sK, 16 * kb + 4 * hh, 16 * kb + 8 + 4 * hh, 32 + cb), f[kb]);
+      }
+    }
+    if (hh == 0) {
+      p.ws.Dbuf[cbase + s * lq_len + qi] = -Dq;
+      p.ws.Lbuf[cbase + s * lq_len + qi] = lse_q * kLog2e - __builtin_amdgcn_logf(ws);
+    }
+    const float dsum = sum32(Dq);
+    if (lane == 0) p.ws.dwp[(tglob * K + s) * 2 + half] = dsum;
+  };
+  for (int r0 = 0; r0 < n; r0 += kPerRound) {
+    if (r0 > 0) block_barrier();  // the last round's tiles have been read
+    const int i0 = r0 + pair * SP;
+    float lse_q[SP];
+#pragma unroll
+    for (int e = 0; e < SP; ++e) lse_q[e] = i0 + e < n ? p.lse[(tok0 + qi) * K + sSlot[i0 + e]] : 0.f;
+#pragma unroll
+    for (int e = 0; e < SP; ++e) {
+      if (i0 + e < n) {
+        const int64_t j = min(max(sJc[i0 + e], 0), (int)p.nKV - 1);
+        T* dst = ring + (pair * SP + e) * (2 * TILE);
+        cp.issue(gk + j * TILE, dst);
+        cp.issue(gv + j * TILE, dst + TILE);
+      }
+    }
+    wait_vmem<0>();
+    block_barrier();
+#pragma unroll
+    for (int e = 0; e < SP; ++e)
+      if (i0 + e < n) run(e, i0 + e, lse_q[e]);
+  }
+
+  // the pairs' partial dQ: part[pair][row][16 float4 blocks], block c of row r at c ^ (r mod 16)
+  block_barrier();
+  float* part = reinterpret_cast<float*>(ring);
+  static_assert(sizeof(ring) >= PAIRS * kS * kD * sizeof(float), "partial dQ fits in the tiles");
+  {
+    const int sw = qi & 15;
+    float* pr = part + (pair * kS + qi) * kD;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      *reinterpret_cast<f32x4*>(pr + 4 * ((2 * g + hh) ^ sw)) =
+          f32x4{g0[4 * g], g0[4 * g + 1], g0[4 * g + 2], g0[4 * g + 3]};
+      *reinterpret_cast<f32x4*>(pr + 4 * ((8 + 2 * g + hh) ^ sw)) =
+          f32x4{g1[4 * g], g1[4 * g + 1], g1[4 * g + 2], g1[4 * g + 3]};
+    }
+  }
+  __syncthreads();
+  constexpr int kTpr = 2 * PAIRS;  // threads per row
+  const int rr = tid / kTpr;
+  T* drow = reinterpret_cast<T*>(p.dq) + (tok0 + rr) * kD;
+  const float as = p.attn_scale;
+#pragma unroll
+  for (int e = 0; e < 16 / kTpr; ++e) {
+    const int cblk = 16 / kTpr * (tid % kTpr) + e;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < PAIRS; ++q)
+      acc += *reinterpret_cast<const f32x4*>(part + (q * kS + rr) * kD + 4 * (cblk ^ (rr & 15)));
+    store4(drow + 4 * cblk, as * acc[0], as * acc[1], as * acc[2], as * acc[3]);
+  }
+}
+
+// Wave pairs per item in the forms above and below for few items: as many as fit in a
+// CU's LDS while every item runs at once (bf16: 4 up to one item per CU, 2 up to two;
+// fp32, whose rounds are five times longer: dQ 4, dK/dV 2 up to two items per CU), else
+// 1, the forms that keep four items per CU.  2.4K tokens (444 items, bf16): dQ 20 -> 14 us
+// and dK/dV 33 -> 24 us a launch (four pairs in two rounds of workgroups took 19 and 31);
+// 16 chunks of one head in fp32: 18 -> 14 and 55 -> 31 us.
+inline int few_pairs(int64_t items, bool bf16) {
+  const int64_t cus = device_cus();
+  if (items > 2 * cus) return 1;
+  return items <= cus || !bf16 ? 4 : 2;
+}
+
 // ---------------------------------------------- key-stationary dK, dV ----
 
 // One workgroup of two waves per (batch, head, key chunk j), four per CU; the pair
@@ -694,16 +896,23 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void bwd_dq_kernel(BwdParams p,
 // j's keys, so a workgroup's barrier couples only its two waves and no partial
 // sums are exchanged.  With the shifted lse L = log2(e) lse - log2(w_s),
 // exp2(S log2(e) scale - L) is w_s P_s directly.
-constexpr int kKvThreads = 128;
-template <typename T, bool XR>
-__global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, int64_t nwork) {
+//
+// PAIRS > 1 (few key chunks): a workgroup of that many wave pairs, each with its own
+// ring, pair i taking retrievers i, i + PAIRS, ...; the pairs' sums are added through LDS
+// in pair order at the end.  A list is a chain of rounds (1.3 us each in bf16, 7 us in
+// fp32), and causal problems have a few long ones (a slice's first chunks), so on a
+// chip with room to spare the longest list is what a launch takes.
+template <typename T, bool XR, int PAIRS>
+__global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) void bwd_dkdv_kernel(BwdParams p, int64_t nwork) {
+  constexpr int kKvThreads = 128 * PAIRS;
+  static_assert(PAIRS == 1 || !XR, "the LMK row staging assumes one pair");
   constexpr int TILE = kS * kD;
   constexpr int SQ = XR ? kS + 1 : kS;  // query rows per chunk
   // ring slot: Q_c tile, dO_c tile, shifted-lse column, D column; with the LMK
   // row also its Q and dO rows and its shifted lse and -D (16 bytes)
   constexpr int XOFF = 2 * TILE + 2 * kS * (int)(sizeof(float) / sizeof(T));
   constexpr int ENTRY = XOFF + (XR ? 2 * kD + 16 / (int)sizeof(T) : 0);
-  __shared__ __attribute__((aligned(16))) T ring[2 * ENTRY];
+  __shared__ __attribute__((aligned(16))) T rings[PAIRS * 2 * ENTRY];
   constexpr int NE = 256;  // retrievers staged in LDS per batch
   __shared__ int sE[NE];
   // LMK rows: up to kXGroup retrievers' rows staged for one padded contraction
@@ -715,7 +924,8 @@ __global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, in
   const int64_t wid = xcd_swizzle(blockIdx.x, gridDim.x);
   if (wid >= nwork) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5;
-  const int half = wave;
+  const int half = PAIRS == 1 ? wave : wave & 1, pair = PAIRS == 1 ? 0 : wave >> 1;
+  T* const ring = rings + pair * 2 * ENTRY;
   const int64_t j = wid % p.nKV;
   const int64_t bh = wid / p.nKV;
   const int h = (int)(bh % p.H);
@@ -756,10 +966,10 @@ __global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, in
   const float* Lb = p.ws.Lbuf + bh * lq_len * K;
   const float* Db = p.ws.Dbuf + bh * lq_len * K;
 
-  const TileCopy<T, 2> cp(wave, lane);
+  const TileCopy<T, 2> cp(half, lane);
   const uint32_t col_off = (uint32_t)(lane * sizeof(float));
   constexpr int kXPieces = kD * (int)sizeof(T) / 16;  // 16-byte pieces of one row
-  const int xw = __builtin_amdgcn_readfirstlane(wave);  // LMK row copies: wave 0 Q and L, wave 1 dO and -D
+  const int xw = __builtin_amdgcn_readfirstlane(half);  // LMK row copies: wave 0 Q and L, wave 1 dO and -D
   const T* const xrow_src = xw == 0 ? qb : ob;
   const float* const xcol_src = xw == 0 ? Lb : Db;
   auto enc = [&](int e) { return ((e / K + p.causal) << 5) | (e % K); };  // list entry t*K+s -> (query chunk << 5) | slot
@@ -770,7 +980,7 @@ __global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, in
     cp.issue(qb + c * SQ * kD, dst);
     cp.issue(ob + c * SQ * kD, dst + TILE);
     float* cols = reinterpret_cast<float*>(dst + 2 * TILE);
-    if (wave == 0) dma_column_s(Lb + s * lq_len + c * SQ, col_off, cols);
+    if (half == 0) dma_column_s(Lb + s * lq_len + c * SQ, col_off, cols);
     else dma_column_s(Db + s * lq_len + c * SQ, col_off, cols + kS);
     if constexpr (XR) {
       // the LMK row (row S of the chunk): wave 0 its Q row and shifted lse, wave 1
@@ -792,7 +1002,7 @@ __global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, in
   // addresses plus an immediate (row +32, key block, dO tile, transposed-row gap)
   constexpr bool kB16 = std::is_same<T, __bf16>::value;
   constexpr uint32_t kTileB = TILE * sizeof(T), kRowB = kD * sizeof(T), kEntryB = ENTRY * sizeof(T);
-  const lds_char* const lds0 = (const lds_char*)(ring);
+  const lds_char* const lds0 = (const lds_char*)(rings) + (uint32_t)pair * 2 * kEntryB;
   uint32_t rofs[4], tofs[2][2];
   {
     const int s16 = lane & 15;
@@ -988,8 +1198,10 @@ __global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, in
   // K/V fragments (round 0's barrier makes them visible)
   for (int b0 = 0; b0 < n; b0 += NE) {
     const int nb = min(NE, n - b0);
+    const int mine = pair < nb ? (nb - pair + PAIRS - 1) / PAIRS : 0;  // this pair's items of the batch
     if (b0 == 0) {
-      issue(0, enc(__builtin_amdgcn_readlane(hv, 2)));
+      static_assert(PAIRS <= kHeadEntries, "every pair's first item is in the header");
+      if (PAIRS == 1 || mine > 0) issue(0, enc(__builtin_amdgcn_readlane(hv, 2 + pair)));
       const int e_head = __shfl(hv, (lane + 2) & 63);  // lane i: header entry i
       if (wave == 0 && lane < kHeadEntries && lane < nb) sE[lane] = enc(e_head);
       for (int i = kHeadEntries + tid; i < nb; i += kKvThreads) sE[i] = enc(list_g[i]);
@@ -997,14 +1209,37 @@ __global__ __launch_bounds__(kKvThreads, 4) void bwd_dkdv_kernel(BwdParams p, in
       __syncthreads();
       for (int i = tid; i < nb; i += kKvThreads) sE[i] = enc(list_g[b0 + i]);
       __syncthreads();
-      issue(0, sE[0]);
+      if (PAIRS == 1 || mine > 0) issue(0, sE[pair]);
     }
-    for (int u = 0; u < nb; ++u) {
+    const int rounds = (nb + PAIRS - 1) / PAIRS;  // the first pair's items: every pair meets its barriers
+    for (int u = 0; u < rounds; ++u) {
       wait_vmem<0>();
       block_barrier();
-      if (u + 1 < nb) issue((u + 1) & 1, sE[u + 1]);
-      run(u & 1, u, u + 1 == nb);
+      if (u + 1 < mine) issue((u + 1) & 1, sE[(u + 1) * PAIRS + pair]);
+      if (PAIRS == 1 || u < mine) run(u & 1, u, u + 1 == nb);
     }
+  }
+  if constexpr (PAIRS > 1) {
+    // the other pairs' sums into the first's, in pair order (the rings are free: every
+    // copy has been waited for)
+    float* part = reinterpret_cast<float*>(rings);
+    static_assert(sizeof(rings) >= (PAIRS - 1) * 2 * 64 * 64 * sizeof(float), "partial sums fit in the rings");
+    auto each = [&](auto f) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        f(dv0, i, i);
+        f(dv1, i, 16 + i);
+        f(dk0, i, 32 + i);
+        f(dk1, i, 48 + i);
+      }
+    };
+    __syncthreads();
+    if (pair > 0)
+      each([&](f32x16& v, int i, int r) { part[(((pair - 1) * 2 + half) * 64 + r) * 64 + lane] = v[i]; });
+    __syncthreads();
+    if (pair > 0) return;
+    for (int q = 0; q < PAIRS - 1; ++q)
+      each([&](f32x16& v, int i, int r) { v[i] += part[((q * 2 + half) * 64 + r) * 64 + lane]; });
   }
 
   // accumulators are transposed: lane holds key kr, d = 32*dt + 8*g + 4*hh + 0..3
@@ -1263,14 +1498,22 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
   auto dq = [&](auto kernel) {
     launch_kernel("bwd_dq_kernel", kernel, dim3((unsigned)dq_wgs), dim3(kThreads), 0, st, p, nq_work);
   };
-  if (s.topk <= kDqStageK)
+  constexpr bool kB16 = sizeof(T) == 2;
+  const int q_pairs = xr ? 1 : few_pairs(nq_work, kB16), k_pairs = xr ? 1 : few_pairs(nk_work, kB16);
+  if (q_pairs > 1)
+    launch_kernel("bwd_dq_kernel", q_pairs == 4 ? bwd_dq_few_kernel<T, 4> : bwd_dq_few_kernel<T, kB16 ? 2 : 4>,
+                  dim3((unsigned)nq_work), dim3(128 * q_pairs), 0, st, p);
+  else if (s.topk <= kDqStageK)
     xr ? dq(bwd_dq_kernel<T, true, true>) : dq(bwd_dq_kernel<T, true, false>);
   else
     xr ? dq(bwd_dq_kernel<T, false, true>) : dq(bwd_dq_kernel<T, false, false>);
-  auto kv = [&](auto kernel) {
-    launch_kernel("bwd_dkdv_kernel", kernel, dim3((unsigned)round8(nk_work)), dim3(kKvThreads), 0, st, p, nk_work);
+  auto kv = [&](auto kernel, int pairs) {
+    launch_kernel("bwd_dkdv_kernel", kernel, dim3((unsigned)round8(nk_work)), dim3(128 * pairs), 0, st, p, nk_work);
   };
-  xr ? kv(bwd_dkdv_kernel<T, true>) : kv(bwd_dkdv_kernel<T, false>);
+  if (xr) kv(bwd_dkdv_kernel<T, true, 1>, 1);
+  else if (k_pairs == 1) kv(bwd_dkdv_kernel<T, false, 1>, 1);
+  else if (kB16 && k_pairs == 4) kv(bwd_dkdv_kernel<T, false, kB16 ? 4 : 2>, 4);
+  else kv(bwd_dkdv_kernel<T, false, 2>, 2);
   const GatherShape gs = gather_shape(s.D, sizeof(T));
   if (dlmk_q) {
     // dsel is formed inside the landmark-query gradient kernel

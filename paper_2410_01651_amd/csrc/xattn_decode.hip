@@ -1,6 +1,7 @@
 // Grouped cross attention for decode (Eq. 2-3 of the method for the one new
 // query chunk of every (batch, head)), with the last step of its retrieval
-// (Eq. 1 top-k) done in the same kernel.
+// (Eq. 1 top-k) done in the same kernel; and, from given lists, for causal problems of
+// few query chunks (launch_xattn_fwd), which leave the chip as empty.
 //
 // Decode has one work item per (batch, head), far too few to fill the chip, so
 // the item is spread over its retrieved chunks instead of over query chunks:
@@ -43,8 +44,8 @@ struct DecParams {
   void* out;
   float* lse;
   float* w;
-  int H, Hr, topk;
-  int64_t nKV;
+  int H, Hr, topk, causal;
+  int64_t nQ, nKV;
   float attn_scale;
   // Gumbel top-k: the lists rank noisy scores, so the chosen chunks' raw scores
   // are recomputed from the landmark rows
@@ -77,10 +78,14 @@ __global__ __launch_bounds__(kDecThreads, (kB16Sp1<T, SP> ? 4 : 2)) void xattn_d
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5;
   const int pair = wave >> 1, half = wave & 1;
-  const int64_t wi = blockIdx.x;  // (batch, head)
-  const int h = (int)(wi % p.H);
-  const int64_t b = wi / p.H;
-  const int64_t row = b * p.Hr + (p.Hr == 1 ? 0 : h);
+  const int64_t wi = blockIdx.x;  // (batch, head, query chunk)
+  const int64_t bh = wi / p.nQ, c = wi % p.nQ;
+  const int h = (int)(bh % p.H);
+  const int64_t b = bh / p.H;
+  // the landmark row that feeds the chunk (causal: the one before; chunk 0 has none)
+  const int64_t slice = b * p.Hr + (p.Hr == 1 ? 0 : h);
+  const bool has_row = !p.causal || c > 0;
+  const int64_t row = slice * p.nQ + (p.causal && has_row ? c - 1 : c);
   const int64_t row_off = row * p.topk;
   const bool owner = p.Hr != 1 || h == 0;  // writes the row's selection and weights
   const int K = p.topk;
@@ -153,7 +158,7 @@ __global__ __launch_bounds__(kDecThreads, (kB16Sp1<T, SP> ? 4 : 2)) void xattn_d
     if (wave == 0) {
       int j = -1;
       float sv = -INFINITY;
-      if (lane < K) {
+      if (has_row && lane < K) {
         j = p.idx[row_off + lane];
         sv = p.sel[row_off + lane];
       }
@@ -173,7 +178,15 @@ __global__ __launch_bounds__(kDecThreads, (kB16Sp1<T, SP> ? 4 : 2)) void xattn_d
         sN = __popcll(mask);
         sValid = (uint32_t)mask;
       }
-      if (owner && p.w && lane < K) p.w[row_off + lane] = wv;
+      if (owner && has_row && p.w && lane < K) p.w[row_off + lane] = wv;
+      if (owner && !has_row && p.w) {
+        // the causal last row feeds no chunk: its weights go out with chunk 0
+        const int64_t last = (slice * p.nQ + p.nQ - 1) * K;
+        float w2;
+        int j2;
+        wave_row_weight(p.idx, p.sel, last, K, p.nKV, w2, j2);
+        if (lane < K) p.w[last + lane] = w2;
+      }
     }
   }
   __syncthreads();
@@ -183,7 +196,7 @@ __global__ __launch_bounds__(kDecThreads, (kB16Sp1<T, SP> ? 4 : 2)) void xattn_d
   const TileCopy<T, 2> cp(half, lane);
   const T* const gk = reinterpret_cast<const T*>(p.k);
   const T* const gv = reinterpret_cast<const T*>(p.v);
-  const int64_t kvb = wi * p.nKV * TILE;  // this (batch, head)'s key/value slice
+  const int64_t kvb = bh * p.nKV * TILE;  // this (batch, head)'s key/value slice
   const lds_char* const lds0 = (const lds_char*)(ring);
   uint32_t kofs[4], vofs[2][2];
   {
@@ -339,7 +352,7 @@ __global__ __launch_bounds__(kDecThreads, (kB16Sp1<T, SP> ? 4 : 2)) void xattn_d
 
 template <typename T, bool OBO, int SP>
 hipError_t launch_dec_sp(const Shape& s, const DecParams& p, hipStream_t st) {
-  const dim3 grid((unsigned)((int64_t)s.B * s.H)), block(kDecThreads);
+  const dim3 grid((unsigned)((int64_t)s.B * s.H * s.nQ)), block(kDecThreads);
   if (p.ls) {
     if (s.topk <= 8)
       launch_kernel("xattn_decode_kernel", xattn_decode_kernel<T, OBO, true, 8, SP>, grid, block, 0, st, p);
@@ -361,7 +374,7 @@ hipError_t launch_dec_sp(const Shape& s, const DecParams& p, hipStream_t st) {
 template <typename T, bool OBO>
 hipError_t launch_dec_t(const Shape& s, const DecParams& p, hipStream_t st) {
   if constexpr (std::is_same<T, __bf16>::value) {
-    if ((int64_t)s.B * s.H <= device_cus()) return launch_dec_sp<T, OBO, 2>(s, p, st);
+    if ((int64_t)s.B * s.H * s.nQ <= device_cus()) return launch_dec_sp<T, OBO, 2>(s, p, st);
   }
   return launch_dec_sp<T, OBO, 1>(s, p, st);
 }
@@ -380,8 +393,8 @@ hipError_t launch_xattn_decode(const Shape& s, const float* list_s, const int* l
   p.q = q; p.k = k; p.v = v;
   p.idx = idx; p.sel = sel;
   p.out = out; p.lse = lse; p.w = w;
-  p.H = s.H; p.Hr = s.Hr; p.topk = s.topk;
-  p.nKV = s.nKV;
+  p.H = s.H; p.Hr = s.Hr; p.topk = s.topk; p.causal = s.causal;
+  p.nQ = s.nQ; p.nKV = s.nKV;
   p.attn_scale = s.attn_scale;
   p.gumbel = list_s != nullptr && s.gumbel;
   p.lmk_q = lmk_q;

@@ -187,3 +187,38 @@ def test_backward_preparation(dev, mode, Hr, nC, k, D, hot):
             glk[r].index_add_(0, j[t], c * lq[0, r, t].double())
     assert max_abs_rel(host64(d["dlmk_q"]), glq[None].cpu().numpy()) <= 1e-5
     assert max_abs_rel(host64(d["dlmk_k"]), glk[None].cpu().numpy()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,H,Hr,nC,k,holes,obo,copies", [
+    ("bf16", 1, 1, 2, 1, False, False, 300),
+    ("bf16", 4, 1, 16, 8, True, True, 9),       # alone: four wave pairs per item
+    ("bf16", 12, 12, 37, 5, True, False, 3),    # two
+    ("bf16", 3, 1, 30, 12, False, False, 12),
+    ("fp32", 1, 1, 16, 2, True, False, 40),
+    ("fp32", 4, 4, 60, 11, True, True, 5),
+])
+def test_few_items_equal_many(dev, dtype, H, Hr, nC, k, holes, obo, copies):
+    """A problem of few items (several wave pairs per query or key chunk) against the same
+    sequence repeated in a batch of many (one pair or wave per chunk)."""
+    import torch
+    from paper_2410_01651_amd import gca
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    idx, sel = _lists(np.random.default_rng(nC), Hr, nC, k, holes)
+    ti, ts = (torch.from_numpy(x.reshape(1, Hr, nC, k)).to(dev) for x in (idx, sel))
+    g = torch.Generator(device=dev).manual_seed(nC + k)
+    q, kk, v, do = (torch.randn(1, H, nC * 64, 64, generator=g, device=dev, dtype=dt) for _ in range(4))
+    got = []
+    for B in (1, copies):
+        rep = lambda x: x.expand(B, *x.shape[1:]).contiguous()  # noqa: E731
+        p = gca.problem(B, H, nC, k, D=64, Hr=Hr, dtype=dtype, off_by_one=obo)
+        a = [rep(x) for x in (q, kk, v, ti, ts)]
+        out, lse, w = gca.grouped_xattn_fwd(p, *a)
+        d = gca.grouped_xattn_bwd(p, *a, lse, rep(do), landmark_grads=False)
+        got.append(dict(out=out, lse=lse, w=w, dq=d["dq"], dk=d["dk"], dv=d["dv"], dsel=d["dsel"]))
+    few, many = got
+    for n in few:
+        # fp32 sums in another order; bf16 results and probabilities rounded from them
+        tol = 1e-6 if n in ("lse", "w") else (2.0 ** -7 if dtype == "bf16" and n != "dsel" else 1e-5)
+        ref = host64(few[n])
+        for b in (0, copies - 1):
+            assert max_abs_rel(host64(many[n][b:b + 1]), ref) <= tol, (n, b)
