@@ -222,3 +222,29 @@ def test_few_items_equal_many(dev, dtype, H, Hr, nC, k, holes, obo, copies):
         ref = host64(few[n])
         for b in (0, copies - 1):
             assert max_abs_rel(host64(many[n][b:b + 1]), ref) <= tol, (n, b)
+
+
+@pytest.mark.parametrize("mode", ["causal", "decode"])
+@pytest.mark.parametrize("nC,k", [(1, 1), (64, 32), (65, 8), (1024, 31), (1100, 1), (3000, 32)])
+def test_topk_adversarial_rows(dev, mode, nC, k):
+    """Rows that ascend (every column beats the ones before), descend, are constant (ties to
+    the lower chunk), mix signs and zeros, or hold infinities and NaN (no candidates)."""
+    import torch
+    from oracle import gca as og
+    from paper_2410_01651_amd import gca
+    rng = np.random.default_rng(nC)
+    nQ = nC if mode == "causal" else 1
+    B = 1 if mode == "causal" else 6
+    r = np.empty((B, 1, nQ, nC), np.float32)
+    for i in range(B * nQ):
+        x = rng.standard_normal(nC)
+        row = [np.sort(x), -np.sort(x), np.full(nC, -1.5), np.sign(x) * rng.integers(0, 3, nC),
+               np.where(x > 0.3, np.inf, np.where(x < -0.5, np.nan, x)), x][i % 6]
+        r.reshape(-1, nC)[i] = row
+    if mode == "causal":
+        r[0, 0][np.triu_indices(nC)] = -np.inf
+    p = gca.problem(B, 1, nC, k, D=64, mode=mode)
+    idx, sel = gca.topk(p, torch.from_numpy(r).to(dev))
+    ref_i, ref_s = og.topk(r.astype(np.float64), k)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ref_i)
+    np.testing.assert_array_equal(host64(sel), ref_s)
