@@ -354,6 +354,54 @@ __device__ __forceinline__ f32x8 lds_frag_t(const float* tile, int r0, int r1, i
   return f;
 }
 
+// Fragments of an fp32 tile at `lds + displacement` from a few per-lane byte offsets
+// computed once (lds_frag / lds_frag_t form an address per element, and held across a
+// loop those take more registers than the fragments): a key block of 16 columns is an
+// exclusive or of bits 6-7 of a row fragment's offset, 32 columns of bit 7 of a column
+// fragment's, and rows + 16 or + 32 are constant displacements (the swizzle repeats every
+// 16 rows).
+struct F32Offsets {
+  uint32_t row[2];  // row l % 32, columns 8 (l / 32) + 0..3 and + 4..7
+  uint32_t col[8];  // rows 4 (l / 32) + 0..3, then the same + 8; column 16 ((l / 16) % 2) + l % 16
+  __device__ __forceinline__ explicit F32Offsets(int lane) {
+    using Z = Swz<float>;
+    const int hh = lane >> 5, c = 16 * ((lane >> 4) & 1) + (lane & 15);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) row[x] = Z::off(lane & 31, 8 * hh + 4 * x) * 4u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      col[e] = Z::off(4 * hh + e, c) * 4u;
+      col[4 + e] = Z::off(8 + 4 * hh + e, c) * 4u;
+    }
+  }
+  // the same offsets as values whose combinations are formed where they are used
+  __device__ __forceinline__ F32Offsets fresh() const {
+    F32Offsets o = *this;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) o.row[x] = (uint32_t)opaque((int)o.row[x]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o.col[e] = (uint32_t)opaque((int)o.col[e]);
+    return o;
+  }
+  // = lds_frag(tile, 32 half + l % 32, 16 kb + 8 (l / 32))
+  __device__ __forceinline__ f32x8 row_frag(const lds_char* tile, int kb, int half) const {
+    typedef const __attribute__((address_space(3))) f32x4 v4;
+    f32x8 f;
+    f.lo = *(v4*)(tile + (row[0] ^ (uint32_t)(kb << 6)) + half * 32 * kD * 4);
+    f.hi = *(v4*)(tile + (row[1] ^ (uint32_t)(kb << 6)) + half * 32 * kD * 4);
+    return f;
+  }
+  // = lds_frag_t(tile, 16 kb + 4 (l / 32), 16 kb + 8 + 4 (l / 32), 32 dh + 16 ((l / 16) % 2))
+  __device__ __forceinline__ f32x8 col_frag(const lds_char* tile, int kb, int dh) const {
+    typedef const __attribute__((address_space(3))) float v1;
+    auto at = [&](int e) { return *(v1*)(tile + (col[e] ^ (uint32_t)(dh << 7)) + kb * 16 * kD * 4); };
+    f32x8 f;
+    f.lo = f32x4{at(0), at(1), at(2), at(3)};
+    f.hi = f32x4{at(4), at(5), at(6), at(7)};
+    return f;
+  }
+};
+
 // ------------------------------------------- one row against a tile ----
 //
 // A single query row (the LMK row of a chunk) against a tile whose fragments a

@@ -750,6 +750,7 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 4 ? 1 : 2) void bwd_dq_few_ke
   const T* const gk = reinterpret_cast<const T*>(p.k) + bh * p.nKV * TILE;
   const T* const gv = reinterpret_cast<const T*>(p.v) + bh * p.nKV * TILE;
   const lds_char* const lds0 = (const lds_char*)(ring);
+  const F32Offsets f32(lane);
   uint32_t kofs[4], tofs[2][2];
   {
     const uint32_t pb = (uint32_t)pair * SP * 2 * kTileB;
@@ -767,13 +768,12 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 4 ? 1 : 2) void bwd_dq_few_ke
     const int s = sSlot[i];
     const float ws = sWc[i];
     const uint32_t co = (uint32_t)slot * 2 * kTileB;
-    const T* sK = ring + (pair * SP + slot) * (2 * TILE);
-    const T* sV = sK + TILE;
+    const lds_char* const tl = lds0 + (uint32_t)(pair * SP + slot) * 2 * kTileB;
     auto row = [&](int kb, int half32, bool v) __device__ -> Frag<T> {
       if constexpr (kB16)
         return lds_b128_at(lds0 + (kofs[kb] + co) + (v ? kTileB : 0u) + half32 * 32 * kRowB);
       else
-        return lds_frag(v ? sV : sK, 32 * half32 + l32, 16 * kb + 8 * hh);
+        return f32.row_frag(tl + (v ? kTileB : 0u), kb, half32);
     };
     f32x16 s0 = zero16(), s1 = zero16(), p0 = zero16(), p1 = zero16();
 #pragma unroll
@@ -782,6 +782,7 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 4 ? 1 : 2) void bwd_dq_few_ke
       mma32(s1, row(kb, 1, false), qf[kb]);
       mma32(p0, row(kb, 0, true), df[kb]);
       mma32(p1, row(kb, 1, true), df[kb]);
+      if (!kB16) __builtin_amdgcn_sched_barrier(0);  // one key block's fragments live at a time
     }
     // as in bwd_dq_kernel
     const float wsf = fmaxf(ws, 1e-30f);
@@ -811,8 +812,9 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 4 ? 1 : 2) void bwd_dq_few_ke
         mma32(g0, lds_tr2(lds0 + (tofs[0][0] + co) + 16 * kb * kRowB, lds0 + (tofs[0][1] + co) + 16 * kb * kRowB), f[kb]);
         mma32(g1, lds_tr2(lds0 + (tofs[1][0] + co) + 16 * kb * kRowB, lds0 + (tofs[1][1] + co) + 16 * kb * kRowB), f[kb]);
       } else {
-        mma32(g0, lds_frag_t(sK, 16 * kb + 4 * hh, 16 * kb + 8 + 4 * hh, cb), f[kb]);
-        mma32(g1, lds_frag_t(sK, 16 * kb + 4 * hh, 16 * kb + 8 + 4 * hh, 32 + cb), f[kb]);
+        mma32(g0, f32.col_frag(tl, kb, 0), f[kb]);
+        mma32(g1, f32.col_frag(tl, kb, 1), f[kb]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     if (hh == 0) {
@@ -875,16 +877,24 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 4 ? 1 : 2) void bwd_dq_few_ke
   }
 }
 
-// Wave pairs per item in the forms above and below for few items: as many as fit in a
-// CU's LDS while every item runs at once (bf16: 4 up to one item per CU, 2 up to two;
-// fp32, whose rounds are five times longer: dQ 4, dK/dV 2 up to two items per CU), else
-// 1, the forms that keep four items per CU.  2.4K tokens (444 items, bf16): dQ 20 -> 14 us
-// and dK/dV 33 -> 24 us a launch (four pairs in two rounds of workgroups took 19 and 31);
-// 16 chunks of one head in fp32: 18 -> 14 and 55 -> 31 us.
+// Wave pairs per item for few items: as many as fit in a CU's LDS while every item runs
+// at once (bf16: 4 up to one item per CU, 2 up to two; fp32, whose rounds are five times
+// longer, 4 up to two), else 1, the form that keeps four items per CU.  2.4K tokens (444
+// items, bf16): dQ 20 -> 14 us and dK/dV 33 -> 24 us a launch (four pairs in two rounds of
+// workgroups took 19 and 31); 16 chunks of one head in fp32: dQ 18 -> 13 us.
 inline int few_pairs(int64_t items, bool bf16) {
   const int64_t cus = device_cus();
   if (items > 2 * cus) return 1;
   return items <= cus || !bf16 ? 4 : 2;
+}
+// The same for dK/dV, whose longest list bounds a causal launch for longer in fp32: 4 up to
+// four items per CU, 2 beyond (start: one pair, two ring slots): 800 items 286 -> 165 us
+// (two pairs 202), 2,000 items 374 -> 343 (four pairs 397), 8,000 items 1,292 -> 1,225.
+// In bf16 one pair is as good or better from three items per CU (1,200 items 47 us
+// each way, 6,400 items 148 against 184 us).
+inline int kv_pairs(int64_t items, bool bf16) {
+  if (bf16) return few_pairs(items, bf16);
+  return items <= 4 * (int64_t)device_cus() ? 4 : 2;
 }
 
 // ---------------------------------------------- key-stationary dK, dV ----
@@ -897,13 +907,19 @@ inline int few_pairs(int64_t items, bool bf16) {
 // sums are exchanged.  With the shifted lse L = log2(e) lse - log2(w_s),
 // exp2(S log2(e) scale - L) is w_s P_s directly.
 //
-// PAIRS > 1 (few key chunks): a workgroup of that many wave pairs, each with its own
+// In fp32 (without the LMK row) a ring has one slot, copied between rounds: a tile pair is
+// 32 KiB and a round's products take five times as long as in bf16, so a second slot
+// hides little, while its LDS holds another pair (two waves per SIMD instead of one).
+template <typename T, bool XR>
+constexpr bool kOneSlot = sizeof(T) == 4 && !XR;
+
+// PAIRS > 1 (kv_pairs): a workgroup of that many wave pairs, each with its own
 // ring, pair i taking retrievers i, i + PAIRS, ...; the pairs' sums are added through LDS
 // in pair order at the end.  A list is a chain of rounds (1.3 us each in bf16, 7 us in
 // fp32), and causal problems have a few long ones (a slice's first chunks), so on a
 // chip with room to spare the longest list is what a launch takes.
 template <typename T, bool XR, int PAIRS>
-__global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) void bwd_dkdv_kernel(BwdParams p, int64_t nwork) {
+__global__ __launch_bounds__(128 * PAIRS, (kOneSlot<T, XR> ? 2 : PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1)) void bwd_dkdv_kernel(BwdParams p, int64_t nwork) {
   constexpr int kKvThreads = 128 * PAIRS;
   static_assert(PAIRS == 1 || !XR, "the LMK row staging assumes one pair");
   constexpr int TILE = kS * kD;
@@ -912,7 +928,9 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
   // row also its Q and dO rows and its shifted lse and -D (16 bytes)
   constexpr int XOFF = 2 * TILE + 2 * kS * (int)(sizeof(float) / sizeof(T));
   constexpr int ENTRY = XOFF + (XR ? 2 * kD + 16 / (int)sizeof(T) : 0);
-  __shared__ __attribute__((aligned(16))) T rings[PAIRS * 2 * ENTRY];
+  // fp32 (without the LMK row): one ring slot, see kOneSlot
+  constexpr int SLOTS = kOneSlot<T, XR> ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) T rings[PAIRS * SLOTS * ENTRY];
   constexpr int NE = 256;  // retrievers staged in LDS per batch
   __shared__ int sE[NE];
   // LMK rows: up to kXGroup retrievers' rows staged for one padded contraction
@@ -925,7 +943,7 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
   if (wid >= nwork) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5;
   const int half = PAIRS == 1 ? wave : wave & 1, pair = PAIRS == 1 ? 0 : wave >> 1;
-  T* const ring = rings + pair * 2 * ENTRY;
+  T* const ring = rings + pair * SLOTS * ENTRY;
   const int64_t j = wid % p.nKV;
   const int64_t bh = wid / p.nKV;
   const int h = (int)(bh % p.H);
@@ -1002,7 +1020,8 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
   // addresses plus an immediate (row +32, key block, dO tile, transposed-row gap)
   constexpr bool kB16 = std::is_same<T, __bf16>::value;
   constexpr uint32_t kTileB = TILE * sizeof(T), kRowB = kD * sizeof(T), kEntryB = ENTRY * sizeof(T);
-  const lds_char* const lds0 = (const lds_char*)(rings) + (uint32_t)pair * 2 * kEntryB;
+  const lds_char* const lds0 = (const lds_char*)(rings) + (uint32_t)pair * SLOTS * kEntryB;
+  const F32Offsets f32(lane);
   uint32_t rofs[4], tofs[2][2];
   {
     const int s16 = lane & 15;
@@ -1014,18 +1033,18 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
       for (int r8 = 0; r8 < 2; ++r8)
         tofs[dh][r8] = Swz<T>::off(8 * r8 + 4 * hh + (s16 >> 2), 32 * dh + cb + 4 * (s16 & 3)) * sizeof(T);
   }
-  auto row_frag = [&](const T* tile, uint32_t so, int kb, int half32) __device__ -> Frag<T> {
+  auto row_frag = [&](uint32_t so, int kb, int half32) __device__ -> Frag<T> {
     if constexpr (kB16) {
       return lds_b128_at(lds0 + (rofs[kb] + so) + half32 * 32 * kRowB);
     } else {
-      return lds_frag(tile, 32 * half32 + (lane & 31), 16 * kb + 8 * hh);
+      return f32.row_frag(lds0 + so, kb, half32);
     }
   };
-  auto col_frag = [&](const T* tile, uint32_t so, int kb, int dh) __device__ -> Frag<T> {
+  auto col_frag = [&](uint32_t so, int kb, int dh) __device__ -> Frag<T> {
     if constexpr (kB16) {
       return lds_tr2(lds0 + (tofs[dh][0] + so) + 16 * kb * kRowB, lds0 + (tofs[dh][1] + so) + 16 * kb * kRowB);
     } else {
-      return lds_frag_t(tile, 16 * kb + 4 * hh, 16 * kb + 8 + 4 * hh, 32 * dh + cb);
+      return f32.col_frag(lds0 + so, kb, dh);
     }
   };
 
@@ -1035,9 +1054,9 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
     const uint32_t qo = (uint32_t)slot * kEntryB, oo = qo + kTileB;
     const float* sL = reinterpret_cast<const float*>(sQ + 2 * TILE);
     const float* sD = sL + kS;
-    if constexpr (XR) {
-      // with the LMK row the 64 queries go in two halves of 32, one after the
-      // other (the same products in the same order per accumulator, half the
+    if constexpr (XR || !kB16) {
+      // with the LMK row, and in fp32, the 64 queries go in two halves of 32, one after
+      // the other (the same products in the same order per accumulator, half the
       // score and dP registers live at a time)
 #pragma unroll
       for (int qh = 0; qh < 2; ++qh) {
@@ -1049,9 +1068,13 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
           for (int r = 0; r < 4; ++r) pp[4 * g + r] = d0[r];
         }
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) mma32(ss, row_frag(sQ, qo, kb, qh), kf[kb]);
+        for (int kb = 0; kb < 4; ++kb) {
+          mma32(ss, row_frag(qo, kb, qh), kf[kb]);
+        }
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) mma32(pp, row_frag(sO, oo, kb, qh), vf[kb]);
+        for (int kb = 0; kb < 4; ++kb) {
+          mma32(pp, row_frag(oo, kb, qh), vf[kb]);
+        }
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 l0 = *reinterpret_cast<const f32x4*>(sL + 32 * qh + 8 * g + 4 * hh);
@@ -1067,13 +1090,13 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
         frag_from_acc(ds2[1], pp, 1, 1.f);
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-          mma32(dv0, col_frag(sO, oo, 2 * qh + kk, 0), wp2[kk]);
-          mma32(dv1, col_frag(sO, oo, 2 * qh + kk, 1), wp2[kk]);
+          mma32(dv0, col_frag(oo, 2 * qh + kk, 0), wp2[kk]);
+          mma32(dv1, col_frag(oo, 2 * qh + kk, 1), wp2[kk]);
         }
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-          mma32(dk0, col_frag(sQ, qo, 2 * qh + kk, 0), ds2[kk]);
-          mma32(dk1, col_frag(sQ, qo, 2 * qh + kk, 1), ds2[kk]);
+          mma32(dk0, col_frag(qo, 2 * qh + kk, 0), ds2[kk]);
+          mma32(dk1, col_frag(qo, 2 * qh + kk, 1), ds2[kk]);
         }
       }
     } else {
@@ -1095,13 +1118,13 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
       f32x16 s0 = zero16(), s1 = zero16();
   #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
-        mma32(s0, row_frag(sQ, qo, kb, 0), kf[kb]);
-        mma32(s1, row_frag(sQ, qo, kb, 1), kf[kb]);
+        mma32(s0, row_frag(qo, kb, 0), kf[kb]);
+        mma32(s1, row_frag(qo, kb, 1), kf[kb]);
       }
   #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
-        mma32(p0, row_frag(sO, oo, kb, 0), vf[kb]);
-        mma32(p1, row_frag(sO, oo, kb, 1), vf[kb]);
+        mma32(p0, row_frag(oo, kb, 0), vf[kb]);
+        mma32(p1, row_frag(oo, kb, 1), vf[kb]);
       }
       // w P (fp32), then dS = w P o (dP - D)
   #pragma unroll
@@ -1131,13 +1154,13 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
       // dV^T += dO^T (w P) and dK^T += Q^T dS  (contractions over the 64 queries)
   #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
-        mma32(dv0, col_frag(sO, oo, kb, 0), wp[kb]);
-        mma32(dv1, col_frag(sO, oo, kb, 1), wp[kb]);
+        mma32(dv0, col_frag(oo, kb, 0), wp[kb]);
+        mma32(dv1, col_frag(oo, kb, 1), wp[kb]);
       }
   #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
-        mma32(dk0, col_frag(sQ, qo, kb, 0), ds[kb]);
-        mma32(dk1, col_frag(sQ, qo, kb, 1), ds[kb]);
+        mma32(dk0, col_frag(qo, kb, 0), ds[kb]);
+        mma32(dk1, col_frag(qo, kb, 1), ds[kb]);
       }
     }
     if constexpr (XR) {
@@ -1213,10 +1236,14 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == 1 ? 4 : PAIRS == 2 ? 2 : 1) v
     }
     const int rounds = (nb + PAIRS - 1) / PAIRS;  // the first pair's items: every pair meets its barriers
     for (int u = 0; u < rounds; ++u) {
+      if (SLOTS == 1 && u > 0) {
+        block_barrier();  // both waves have read the slot
+        if (u < mine) issue(0, sE[u * PAIRS + pair]);
+      }
       wait_vmem<0>();
       block_barrier();
-      if (u + 1 < mine) issue((u + 1) & 1, sE[(u + 1) * PAIRS + pair]);
-      if (PAIRS == 1 || u < mine) run(u & 1, u, u + 1 == nb);
+      if (SLOTS == 2 && u + 1 < mine) issue((u + 1) & 1, sE[(u + 1) * PAIRS + pair]);
+      if (PAIRS == 1 || u < mine) run(SLOTS == 2 ? u & 1 : 0, u, u + 1 == nb);
     }
   }
   if constexpr (PAIRS > 1) {
@@ -1499,7 +1526,7 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
     launch_kernel("bwd_dq_kernel", kernel, dim3((unsigned)dq_wgs), dim3(kThreads), 0, st, p, nq_work);
   };
   constexpr bool kB16 = sizeof(T) == 2;
-  const int q_pairs = xr ? 1 : few_pairs(nq_work, kB16), k_pairs = xr ? 1 : few_pairs(nk_work, kB16);
+  const int q_pairs = xr ? 1 : few_pairs(nq_work, kB16), k_pairs = xr ? 1 : kv_pairs(nk_work, kB16);
   if (q_pairs > 1)
     launch_kernel("bwd_dq_kernel", q_pairs == 4 ? bwd_dq_few_kernel<T, 4> : bwd_dq_few_kernel<T, kB16 ? 2 : 4>,
                   dim3((unsigned)nq_work), dim3(128 * q_pairs), 0, st, p);
@@ -1511,9 +1538,9 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
     launch_kernel("bwd_dkdv_kernel", kernel, dim3((unsigned)round8(nk_work)), dim3(128 * pairs), 0, st, p, nk_work);
   };
   if (xr) kv(bwd_dkdv_kernel<T, true, 1>, 1);
-  else if (k_pairs == 1) kv(bwd_dkdv_kernel<T, false, 1>, 1);
-  else if (kB16 && k_pairs == 4) kv(bwd_dkdv_kernel<T, false, kB16 ? 4 : 2>, 4);
-  else kv(bwd_dkdv_kernel<T, false, 2>, 2);
+  else if (k_pairs == 4) kv(bwd_dkdv_kernel<T, false, 4>, 4);
+  else if (k_pairs == 2) kv(bwd_dkdv_kernel<T, false, 2>, 2);
+  else kv(bwd_dkdv_kernel<T, false, kB16 ? 1 : 2>, kB16 ? 1 : 2);
   const GatherShape gs = gather_shape(s.D, sizeof(T));
   if (dlmk_q) {
     // dsel is formed inside the landmark-query gradient kernel

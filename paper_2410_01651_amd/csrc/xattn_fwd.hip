@@ -82,12 +82,18 @@ __device__ __forceinline__ RowMeta load_row_meta(const FwdParams& p, int64_t row
 }
 
 template <typename T, bool OBO, bool XR>
-__global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && !XR ? 2 : kWgPerCu)) void xattn_fwd_kernel(FwdParams p) {
   constexpr int TILE = kS * kD;
   constexpr int SQ = XR ? kS + 1 : kS;  // query rows per chunk
   static_assert(kPairs == 1, "the LMK row exchange assumes one pair per workgroup");
   __shared__ __attribute__((aligned(16))) LmkShared<T> sX[1];  // used with XR only
-  __shared__ __attribute__((aligned(16))) T ring[kPairs * 2 * 2 * TILE];  // pair p: slots 2p, 2p+1 (K and V tiles)
+  // In fp32 a tile pair is 32 KiB and a round's products take five times as long as in
+  // bf16, so a second ring slot hides little and costs the second wave per SIMD (two
+  // workgroups per CU instead of four): one slot, copied between rounds while the CU's
+  // other workgroups compute (2,000 chunks, k = 8: 182 -> 165 us; 8,000: 666 -> 609).  With the LMK row the registers of a second wave
+  // are not there either way.
+  constexpr bool ONE = sizeof(T) == 4 && !XR;
+  __shared__ __attribute__((aligned(16))) T ring[kPairs * (ONE ? 1 : 2) * 2 * TILE];  // pair p: slots 2p, 2p+1 (K and V tiles)
   __shared__ int sJ[kPairs][2][32];     // [pair][chunk parity][slot]: chunk index or -1
   __shared__ int sSlot[kPairs][2][32];  // compacted lists of the valid slots: slot, chunk, weight
   __shared__ int sJc[kPairs][2][32];
@@ -222,6 +228,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
   constexpr bool kB16 = std::is_same<T, __bf16>::value;
   constexpr uint32_t kTileB = TILE * sizeof(T), kRowB = kD * sizeof(T);
   const lds_char* const lds0 = (const lds_char*)(ring);
+  const F32Offsets f32o(lane);  // used with ONE
   uint32_t kofs[4], vofs[2][2];
   {
     const uint32_t pb = (uint32_t)pair * 4 * kTileB;
@@ -241,15 +248,18 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
   float ox0 = 0.f, ox1 = 0.f;  // LMK row: this lane's partial outputs for d = l%32 and 32 + l%32
   auto compute = [&](int slot, int u, int64_t tok0, int buf, f32x16& o0, f32x16& o1) __device__ {
     const uint32_t co = (uint32_t)slot * 2 * kTileB;
+    const F32Offsets f32 = ONE ? f32o.fresh() : f32o;
     const int s = __builtin_amdgcn_readlane(ls, u);
     const bool xr = XR && (u & 1) == xh;  // this wave takes the LMK row of slot u
     const T* sK = ring + (2 * pair + slot) * (2 * TILE);
     const T* sV = sK + TILE;
     // all K fragments first, so the eight products issue back to back
-    Frag<T> ka[8];
+    Frag<T> ka[ONE ? 1 : 8];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
-      if constexpr (kB16) {
+      if constexpr (ONE) {
+        // (read where they are used)
+      } else if constexpr (kB16) {
         const lds_char* kp = lds0 + (kofs[kb] + co);
         ka[2 * kb] = lds_b128_at(kp);
         ka[2 * kb + 1] = lds_b128_at(kp + 32 * kRowB);
@@ -261,8 +271,13 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
     f32x16 st0 = zero16(), st1 = zero16();
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
-      mma32(st0, ka[2 * kb], qf[kb]);
-      mma32(st1, ka[2 * kb + 1], qf[kb]);
+      if constexpr (ONE) {
+        mma32(st0, f32.row_frag(lds0, kb, 0), qf[kb]);
+        mma32(st1, f32.row_frag(lds0, kb, 1), qf[kb]);
+      } else {
+        mma32(st0, ka[2 * kb], qf[kb]);
+        mma32(st1, ka[2 * kb + 1], qf[kb]);
+      }
     }
     // LMK row scores while the products run: lane l holds keys l%32 and 32 + l%32
     // over its half of the dimensions; the halves are added across l ^ 32
@@ -280,10 +295,11 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
       xs = hh ? a1 : a0;  // the score of key `lane`
     }
     // V^T fragments are read while the softmax runs
-    Frag<T> va[8];
+    Frag<T> va[ONE ? 1 : 8];
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
-      if constexpr (kB16) {
+      if constexpr (ONE) {
+      } else if constexpr (kB16) {
         va[2 * kb] = lds_tr2(lds0 + (vofs[0][0] + co) + 16 * kb * kRowB, lds0 + (vofs[0][1] + co) + 16 * kb * kRowB);
         va[2 * kb + 1] =
             lds_tr2(lds0 + (vofs[1][0] + co) + 16 * kb * kRowB, lds0 + (vofs[1][1] + co) + 16 * kb * kRowB);
@@ -330,8 +346,13 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
     frag_from_acc(pf[3], st1, 1, coef);
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
-      mma32(o0, va[2 * kb], pf[kb]);
-      mma32(o1, va[2 * kb + 1], pf[kb]);
+      if constexpr (ONE) {
+        mma32(o0, f32.col_frag(lds0 + kTileB, kb, 0), pf[kb]);
+        mma32(o1, f32.col_frag(lds0 + kTileB, kb, 1), pf[kb]);
+      } else {
+        mma32(o0, va[2 * kb], pf[kb]);
+        mma32(o1, va[2 * kb + 1], pf[kb]);
+      }
     }
     if (xr) {
       // LMK row output: (w P) V against the V^T fragments, read again now that
@@ -371,7 +392,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
       wait_vmem<0>();
       block_barrier();
       if (u == 0) {
-        if (!XR && ci > 0 && live) {
+        if (!XR && !ONE && ci > 0 && live) {
 #pragma unroll
           for (int kb = 0; kb < 4; ++kb) qf[kb] = qn[kb];
         }
@@ -382,7 +403,8 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
           kvb = kvb_n;
         }
         if (live_next) {
-          if constexpr (!XR) {
+          if constexpr (ONE) {
+          } else if constexpr (!XR) {
             const T* qr = qrow_ptr(w_next);
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) qn[kb] = load_frag(qr + 16 * kb + 8 * hh);
@@ -401,13 +423,17 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
         if (K == 1) block_barrier();  // the next chunk's list is needed this round
       }
       const bool comp = u < n;
-      const int is = comp ? cs ^ 1 : cs;
+      const int is = comp && !ONE ? cs ^ 1 : cs;
+      if (ONE && comp) {
+        compute(cs, u, tok0, buf, o0, o1);
+        block_barrier();  // both waves have read the slot
+      }
       if (u + 1 < n) {
         issue_item(kvb, __builtin_amdgcn_readlane(lj, u + 1), is);
       } else if (u == K - 1 && live_next && sN[pair][buf ^ 1] > 0) {
         issue_item(kvb_n, sJc[pair][buf ^ 1][0], is);
       }
-      if (comp) {
+      if (!ONE && comp) {
         compute(cs, u, tok0, buf, o0, o1);
         cs ^= 1;
       }
@@ -415,7 +441,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void xattn_fwd_kernel(FwdParams
     // with the LMK row the next chunk's Q rows are loaded only now, straight into
     // the fragments (the registers of a prefetch are what the row's own work
     // needs); the next round's wait covers them
-    if (XR && live_next) {
+    if ((XR || ONE) && live_next) {
       const T* qr = qrow_ptr(w_next);
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) qf[kb] = load_frag(qr + 16 * kb + 8 * hh);
