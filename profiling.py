@@ -43,10 +43,13 @@ def source_hash() -> str:
 
 
 def short_name(kernel: str) -> str:
+    # forms that the library launches under one name
+    for form, key in (("xattn_fwd_wave_kernel", "xattn_fwd_kernel"), ("bwd_dq_few_kernel", "bwd_dq_kernel")):
+        if form in kernel:
+            return key
     for key in ("xattn_fwd_kernel", "bwd_dq_kernel", "bwd_dkdv_kernel", "chunk_scores_kernel", "topk_kernel",
-                "fused_select_kernel", "select_part_kernel", "select_merge_kernel", "decode_scan_kernel", "xattn_decode_kernel", "weights_kernel",
-                "fill_zero_kernel", "csr_count_kernel", "csr_scan_kernel", "csr_fill_kernel", "csr_sort_kernel",
-                "dsel_kernel", "dlmk_q_kernel", "dlmk_k_kernel"):
+                "fused_select_kernel", "sel_clear_kernel", "select_part_kernel", "select_wide_kernel", "select_merge_kernel",
+                "decode_scan_kernel", "xattn_decode_kernel", "bwd_prep_kernel", "dsel_kernel", "dlmk_q_kernel", "dlmk_k_kernel"):
         if key in kernel:
             return key
     if "copy" in kernel.lower():
