@@ -812,6 +812,7 @@ __global__ __launch_bounds__(64, 2) void xattn_fwd_wave_kernel(FwdParams p) {
       x0 = x1;
       rest = x0.mask;
       more = discover(x1);
+      if (!more) x1 = x0;  // an empty chunk's mask names no tile to copy
     }
   }
   wait_tiles<0>();  // no copy outlives the workgroup's LDS

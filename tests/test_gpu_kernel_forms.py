@@ -70,6 +70,38 @@ def test_forward_wave_form_equals_pair_form(dev, B, H, Hr, nC, k, holes, obo):
     assert max_abs_rel(w0, w1) <= 1e-6
 
 
+@pytest.mark.parametrize("B,H,nC,first_empty", [
+    (1, 1000, 3, 3),      # streams that end with a sequence's chunks 0 and 1
+    (1, 3, 1400, 500),    # lists that are all pads from a row on: streams with empty chunks at their end
+    (2, 1, 1500, 2),      # one chunk that retrieves anything per sequence
+    (1, 1, 2300, 900),    # the same in window order
+])
+def test_forward_streams_ending_in_empty_chunks(dev, B, H, nC, first_empty):
+    """A persistent stream whose last chunks retrieve nothing: their zeros are written, and the
+    last chunk before them is as on the pair form."""
+    import torch
+    from paper_2410_01651_amd import gca
+    k = 4
+    rng = np.random.default_rng(nC)
+    idx = np.full((B, 1, nC, 9), -1, np.int32)
+    sel = np.full((B, 1, nC, 9), -np.inf, np.float32)
+    for t in range(1, min(first_empty, nC)):
+        n = min(t, k)
+        idx[:, 0, t, :n] = np.sort(rng.choice(t, size=n, replace=False))
+        sel[:, 0, t, :n] = rng.standard_normal((B, n))
+    g = torch.Generator(device=dev).manual_seed(nC)
+    q, kk, v = (torch.randn(B, H, nC * 64, 64, generator=g, device=dev, dtype=torch.bfloat16) for _ in range(3))
+    got = []
+    for K in (k, 9):
+        i, s = (torch.from_numpy(np.ascontiguousarray(x[..., :K])).to(dev) for x in (idx, sel))
+        out, lse, w = gca.grouped_xattn_fwd(gca.problem(B, H, nC, K, D=64), q, kk, v, i, s)
+        got.append((host64(out), host64(lse)[..., :k], host64(w)[..., :k]))
+    for a, b, tol in zip(*got, (2.0 ** -7, 1e-6, 1e-6)):   # as above
+        assert max_abs_rel(a, b) <= tol
+    empty = got[0][0].reshape(B, H, nC, 64 * 64)[:, :, min(first_empty, nC) + 1:]
+    assert not empty.any()
+
+
 @pytest.mark.parametrize("dtype,D,nC,k,gumbel", [
     ("bf16", 576, 1, 3, False),
     ("bf16", 1024, 129, 8, False),       # two row blocks, the second of one row; a ragged second key tile
