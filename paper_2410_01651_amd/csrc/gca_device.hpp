@@ -1036,12 +1036,14 @@ __device__ void merge_lists(const float* __restrict__ ls, const int* __restrict_
     wave_top_one(cs, cj, K, ms, mj, cnt);
   } else {
     L.init();
-    for (int e = lane; e < ne; e += 64) {
-      const int src = e / K;
-      const int64_t l = scan_list_of(__shfl(mj, src), pw);
-      const int64_t off = l * K + (e - src * K);
-      const int jj = rj[off];
-      if (jj >= 0) L.insert(rs[off], jj);
+    for (int e0 = 0; e0 < ne; e0 += 64) {
+      const int e = e0 + lane, src = e < ne ? e / K : 0;
+      const int head = __shfl(mj, src);  // every lane takes part in the exchange
+      if (e < ne) {
+        const int64_t off = scan_list_of(head, pw) * K + (e - src * K);
+        const int jj = rj[off];
+        if (jj >= 0) L.insert(rs[off], jj);
+      }
     }
     wave_merge(L, K, ms, mj, cnt);
   }

@@ -158,6 +158,38 @@ def test_decode_large_batch_equals_small(dev, B, H, nC, k, obo):
                 assert max_abs_rel(host64(a), host64(b)) <= tol, n
 
 
+@pytest.mark.parametrize("B,nC,k,pw", [(4, 8192, 14, 32), (4, 8192, 18, 32), (4, 8192, 27, 32), (4, 8000, 32, 32),
+                                       (18, 896, 10, 16), (11, 2200, 22, 24), (2, 1000, 9, 8)])
+def test_decode_winners_in_one_scan_list(dev, B, nC, k, pw):
+    """Most of a row's best k in the scan's first list (chunks c < 4 pw with c mod 32 < 8, pw
+    chunks per list), and list counts whose entries leave the merge's last step of 64 lanes
+    partial.  Scores are small whole numbers, so the selection is exact."""
+    import torch
+    from oracle import gca as og
+    from paper_2410_01651_amd import gca
+    rng = np.random.default_rng(nC + k)
+    D = 64
+    val = -rng.integers(1, 256, (B, nC)).astype(np.float32)
+    first = np.arange(nC)[(np.arange(nC) < 4 * pw) & (np.arange(nC) % 32 < 8)]
+    for b in range(B):
+        n = min(len(first), k + 2)
+        val[b, rng.choice(first, n, replace=False)] = 1 + rng.permutation(n)
+        val[b, rng.integers(nC)] = 40
+    lk = np.zeros((B, 1, nC, D), np.float32)
+    lk[:, 0, :, 3] = val
+    lq = np.zeros((B, 1, 1, D), np.float32)
+    lq[..., 3] = 8.0
+    g = torch.Generator(device=dev).manual_seed(nC)
+    q = torch.randn(B, 1, 64, 64, generator=g, device=dev, dtype=torch.bfloat16)
+    kk, v = (torch.randn(B, 1, nC * 64, 64, generator=g, device=dev, dtype=torch.bfloat16) for _ in range(2))
+    p = gca.problem(B, 1, nC, k, D=D, mode="decode")  # score scale 1/8
+    up = lambda a: torch.from_numpy(a).to(dev).bfloat16()  # noqa: E731
+    f = gca.forward(p, up(lq), up(lk), q, kk, v)
+    ref_i, ref_s = og.topk(val[:, None, None, :].astype(np.float64), k)
+    np.testing.assert_array_equal(f["idx"].cpu().numpy(), ref_i)
+    np.testing.assert_array_equal(host64(f["sel"]), ref_s)
+
+
 @pytest.mark.parametrize("mode,Hr,nC,k,D,hot", [
     ("causal", 1, 2, 1, 64, False),
     ("causal", 1, 17, 3, 64, False),       # a second group of one chunk
