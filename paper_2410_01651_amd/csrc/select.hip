@@ -33,6 +33,7 @@ template <typename T> struct SelMax;
 template <> struct SelMax<__bf16> { static constexpr int kCh = 8; };  // D <= 512 in registers
 template <> struct SelMax<float> { static constexpr int kCh = 4; };   // D <= 256
 constexpr int kSelThreads = 256;
+constexpr float kMaxFloat = 3.402823466e38f;  // the largest finite score
 constexpr int kSelWaves = kSelThreads / 64;
 static_assert(kSelWaves * 32 == kSelRows, "one 32-row column block per wave");
 
@@ -100,7 +101,7 @@ __device__ __forceinline__ float sel_threshold(uint32_t own, uint32_t pub) {
   uint32_t qa, qb;
   pair32(pub, qa, qb);
   const uint32_t hi = max(own, max(qa, qb));  // the best threshold's score bits
-  return hi == 0u ? -INFINITY : key_score((uint64_t)hi << 32);
+  return hi == 0u ? -kMaxFloat : key_score((uint64_t)hi << 32);
 }
 
 // Folds the 16 scores a lane holds of 32 keys from key0 (row t's, S^T in the
@@ -109,7 +110,9 @@ __device__ __forceinline__ float sel_threshold(uint32_t own, uint32_t pub) {
 // into its list.  The candidates are filtered against the threshold into a bit mask;
 // then every lane inserts its surviving candidates one per round, so a round costs one
 // insert for the wave however many rows have a survivor, and the wave runs as many
-// rounds as its lane with the most survivors.  full: every key is a candidate.
+// rounds as its lane with the most survivors.  Only finite scores (with noise) are
+// candidates: a threshold is never below the lowest finite value, which drops -inf and
+// NaN in the filter, and +inf is dropped at its insertion.  full: every key is in range.
 template <int KM, bool GUMBEL>
 __device__ __forceinline__ void sel_fold(const SelParams& p, TopKeys<KM>& L, f32x16 a, int64_t key0, int64_t bhr,
                                          int64_t t, float ts, bool full) {
@@ -147,7 +150,8 @@ __device__ __forceinline__ void sel_fold(const SelParams& p, TopKeys<KM>& L, f32
 #pragma unroll
       for (int e = 0; e < 2; ++e) v2[e] = (i & 4) ? v4[2 * e + 1] : v4[2 * e];
       const float v = (i & 8) ? v2[1] : v2[0];
-      L.insert(pack_key(v, (int)(key0 + 8 * (i >> 2) + 4 * hh + (i & 3))));
+      // (the empty key displaces nothing)
+      L.insert(v <= kMaxFloat ? pack_key(v, (int)(key0 + 8 * (i >> 2) + 4 * hh + (i & 3))) : 0);
     }
   }
 }

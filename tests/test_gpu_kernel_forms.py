@@ -133,6 +133,45 @@ def test_wide_select_equals_score_matrix(dev, dtype, D, nC, k, gumbel):
         assert max_abs_rel(got["split"][1], got[name][1]) <= 1e-5
 
 
+@pytest.mark.parametrize("dtype,D,nC,k,gumbel", [
+    ("bf16", 64, 300, 8, False), ("bf16", 512, 150, 16, True), ("fp32", 256, 200, 5, False),   # queries in registers
+    ("bf16", 576, 300, 8, False), ("bf16", 1024, 150, 16, True), ("fp32", 320, 200, 5, False),  # both through LDS
+])
+def test_select_without_matrix_takes_finite_scores_only(dev, dtype, D, nC, k, gumbel):
+    """Scores that overflow to +inf and -inf are no candidates, in rows with and without k finite
+    ones, for every form of the selection.  (Wide landmarks run one pass when the output overlaps
+    an input; narrow ones only for k > 16.)"""
+    import torch
+    from paper_2410_01651_amd import gca
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng(D + nC)
+    lk = np.zeros((1, 2, nC, D), np.float32)
+    lq = np.zeros((1, 2, nC, D), np.float32)
+    big = rng.random((1, 2, nC)) < np.where(np.arange(nC) < 40, 0.9, 0.2)
+    # distinct whole numbers, and values that 16 overflows and 1/2 does not
+    whole = np.stack([rng.permutation(nC) - nC // 2 for _ in range(2)])[None]
+    lk[..., 3] = np.where(big, rng.choice([-3e38, 3e38], big.shape), whole)
+    lq[..., 3] = rng.choice([16.0, 16.0, 0.5, 0.0], (1, 2, nC))
+    g = torch.Generator(device=dev).manual_seed(D)
+    q, kk, v = (torch.randn(1, 2, nC * 64, 64, generator=g, device=dev, dtype=dt) for _ in range(3))
+    tq, tk = (torch.from_numpy(a).to(dev).to(dt) for a in (lq, lk))
+    seed = 5 if gumbel else None
+    got = {}
+    for name, flags, out in (("split", gca.FLAG_FUSED_TOPK, None), ("matrix", gca.FLAG_MATERIALIZE, None),
+                             ("overlap", gca.FLAG_FUSED_TOPK, q)):
+        p = gca.problem(1, 2, nC, k, D=D, Hr=2, dtype=dtype, flags=flags, gumbel_seed=seed)
+        f = gca.forward(p, tq, tk, q, kk, v, out=out)
+        got[name] = f["idx"].cpu().numpy(), host64(f["sel"])
+    with np.errstate(over="ignore"):
+        sc = (host64(tq)[..., 3][..., :, None] * host64(tk)[..., 3][..., None, :]).astype(np.float32)
+    cand = np.isfinite(sc) & np.tri(nC, k=-1, dtype=bool)
+    for name, (i, s) in got.items():
+        assert np.array_equal((i >= 0).sum(-1), np.minimum(cand.sum(-1), k)), name
+        assert np.isfinite(s[i >= 0]).all(), name
+        np.testing.assert_array_equal(i, got["matrix"][0])
+        np.testing.assert_array_equal(s, got["matrix"][1])
+
+
 @pytest.mark.parametrize("B,H,nC,k,obo", [(65, 4, 40, 8, False), (20, 13, 9, 12, True), (130, 2, 33, 32, False),
                                           (300, 1, 3, 5, False)])
 def test_decode_large_batch_equals_small(dev, B, H, nC, k, obo):
