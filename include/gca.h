@@ -238,7 +238,8 @@ int gca_profile_count(void);
 const char* gca_profile_name(int i);
 
 /* Bytes of workspace `op` (GCA_OP_FORWARD or GCA_OP_BACKWARD) needs for problem p;
- * 0 if p is invalid or needs none. */
+ * 0 if p is invalid or needs none.  In DECODE mode the forward's size never falls as
+ * n_chunks grows: a workspace sized for the longest past serves every shorter one. */
 size_t gca_workspace_size(const gca_problem* p, int op);
 
 /* Static description of a status code. */

@@ -1,5 +1,6 @@
 // Workspace plans and device facts shared by the C ABI and the launchers (host
 // code only).
+#include <algorithm>
 #include <atomic>
 
 #include "gca_plan.hpp"
@@ -29,23 +30,33 @@ int device_cus() {
 
 // ----------------------------------------------------------- decode ----
 
+namespace {
+constexpr int64_t kScanTarget = 256, kScanWaves = 4;
+}
+
 DecodePlan decode_plan(const Shape& s) {
   // about 256 scan workgroups in all, every wave at least one group of 8 keys
-  constexpr int64_t kWaves = 4;
   const int64_t rows = (int64_t)s.B * s.Hr;
-  int64_t wgs = 256 / rows;
+  int64_t wgs = kScanTarget / rows;
   if (wgs < 1) wgs = 1;
-  int64_t pw = (s.nKV + wgs * kWaves - 1) / (wgs * kWaves);
+  int64_t pw = (s.nKV + wgs * kScanWaves - 1) / (wgs * kScanWaves);
   pw = (pw + 7) & ~int64_t(7);
   DecodePlan p;
   p.pw = pw;
-  p.wgs = ((s.nKV + pw - 1) / pw + kWaves - 1) / kWaves;
-  p.lists = p.wgs * kWaves;  // a wave whose groups all lie past the keys leaves an empty list
+  p.wgs = ((s.nKV + pw - 1) / pw + kScanWaves - 1) / kScanWaves;
+  p.lists = p.wgs * kScanWaves;  // a wave whose groups all lie past the keys leaves an empty list
   return p;
 }
 
+// Sized by the most lists that any past of up to nKV chunks needs, which grows with nKV
+// (the plan's own count falls wherever pw steps up), so that one workspace sized for a
+// program's longest past serves every shorter one.
 size_t decode_workspace(const Shape& s) {
-  const size_t n = (size_t)s.B * s.Hr * decode_plan(s).lists * s.topk;
+  const int64_t rows = (int64_t)s.B * s.Hr;
+  const int64_t most = rows < kScanTarget ? kScanTarget / rows : 1;  // workgroups per row
+  // a workgroup's waves take 8 chunks or more each
+  const int64_t wgs = std::min(most, (s.nKV + 8 * kScanWaves - 1) / (8 * kScanWaves));
+  const size_t n = (size_t)(rows * wgs * kScanWaves) * s.topk;
   return align256(n * sizeof(float)) + align256(n * sizeof(int));
 }
 float* decode_list_scores(const Shape&, void* ws) { return reinterpret_cast<float*>(ws); }
