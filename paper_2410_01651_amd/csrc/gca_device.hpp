@@ -201,6 +201,15 @@ __device__ __forceinline__ void wait_tiles() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Orders a wave's LDS accesses on either side against each other, across lanes: the LDS
+// takes one wave's operations in program order, so this only keeps the compiler from
+// moving or keeping a lane's access across another lane's (no instructions).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Workgroup barrier that leaves vector-memory operations (the asynchronous tile
 // copies) in flight: it first drains this wave's LDS operations, so that LDS
 // written before the barrier is visible to every wave after it (s_barrier alone

@@ -126,8 +126,10 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
            (uint32_t)__builtin_amdgcn_readlane((int)k, K - 1);
   };
   auto flush = [&]() {
-    // (a wave's own LDS writes are read back in program order)
-    best = wave_sort_desc(lane < K ? best : lane - K < held ? sKey[wave][lane] : 0);
+    wave_lds_order();  // other lanes appended the keys ...
+    const uint64_t appended = lane - K < held ? sKey[wave][lane] : 0;
+    wave_lds_order();  // ... and the next ones are appended after this read
+    best = wave_sort_desc(lane < K ? best : appended);
     held = 0;
     floor_ = max(floor_, kth(best));
   };
