@@ -745,9 +745,11 @@ __global__ __launch_bounds__(64, 2) void xattn_fwd_wave_kernel(FwdParams p) {
 #pragma unroll 1
       for (int s = 0; x0.mask != full && s < K; ++s)
         if (!((x0.mask >> s) & 1u)) sLse[half][l32 * K + s] = -INFINITY;
+      wave_lds_order();  // other lanes' log-sum-exps ...
       float v[kWaveMaxK / 2];
 #pragma unroll
       for (int i = 0; i < kWaveMaxK / 2; ++i) v[i] = sLse[half][64 * i + lane];
+      wave_lds_order();  // ... which the next chunk's overwrite after this
       float* lse = p.lse + tok * K;
 #pragma unroll
       for (int i = 0; i < kWaveMaxK / 2; ++i)
