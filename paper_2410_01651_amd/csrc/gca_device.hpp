@@ -736,6 +736,7 @@ __device__ __forceinline__ bool better(float s, int j, float s2, int j2) {
 }
 
 constexpr int kNoChunk = 0x7fffffff;
+constexpr float kMaxFloat = 3.402823466e38f;  // the largest finite score: only finite scores are candidates
 
 // A lane's running best-KM list, sorted best first, in registers.
 template <int KM>
@@ -780,15 +781,17 @@ __device__ __forceinline__ void take_better(float& s, int& j, float os, int oj) 
 // negative ones; -0 is taken as +0) above the complemented chunk index, so the
 // larger key is the better candidate and the empty entry (-inf, kNoChunk) is
 // below every real one.
-__device__ __forceinline__ uint64_t pack_key(float s, int j) {
-  uint32_t u = s == 0.f ? 0u : __float_as_uint(s);
-  u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-  return ((uint64_t)u << 32) | (uint64_t)(~(uint32_t)j);
+__device__ __forceinline__ uint32_t order_bits(float s) {
+  const uint32_t u = s == 0.f ? 0u : __float_as_uint(s);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-__device__ __forceinline__ float key_score(uint64_t k) {
-  const uint32_t u = (uint32_t)(k >> 32);
+__device__ __forceinline__ float order_score(uint32_t u) {
   return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
+__device__ __forceinline__ uint64_t pack_key(float s, int j) {
+  return ((uint64_t)order_bits(s) << 32) | (uint64_t)(~(uint32_t)j);
+}
+__device__ __forceinline__ float key_score(uint64_t k) { return order_score((uint32_t)(k >> 32)); }
 __device__ __forceinline__ int key_chunk(uint64_t k) { return (int)~(uint32_t)k; }
 
 // A lane's running best-KM list as packed candidate keys (pack_key), sorted
@@ -871,6 +874,27 @@ __device__ __forceinline__ uint64_t wave_sort_desc(uint64_t k) {
         else b = dpp64<kDppRor8>(k);  // j == 8: rotating a 16-lane row by 8 pairs l with l ^ 8
       }
       k = ((a > b) == keep_max) ? a : b;  // the larger key where the lane keeps the max
+    }
+  }
+  return k;
+}
+
+// The same of one 32-bit value per lane.
+__device__ __forceinline__ uint32_t wave_sort_desc(uint32_t k) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int kk = 2; kk <= 64; kk <<= 1) {
+#pragma unroll
+    for (int j = kk >> 1; j > 0; j >>= 1) {
+      const bool keep_max = ((lane & j) == 0) == ((lane & kk) == 0);
+      uint32_t a = k, b;
+      if (j == 32) pair32(k, a, b);
+      else if (j == 16) pair16(k, a, b);
+      else if (j == 1) b = dpp<kDppXor1>(k);
+      else if (j == 2) b = dpp<kDppXor2>(k);
+      else if (j == 4) b = swz_xor4(k);
+      else b = dpp<kDppRor8>(k);
+      k = keep_max ? max(a, b) : min(a, b);
     }
   }
   return k;

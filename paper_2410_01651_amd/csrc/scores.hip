@@ -98,13 +98,18 @@ __global__ __launch_bounds__(256) void chunk_scores_kernel(const T* __restrict__
 // ------------------------------------------------------------- top-k ----
 
 // One wave per row, its columns in batches of 64 kTB.  The row's best K so far are kept
-// one per lane, sorted (packed keys, lane r: the r-th).  A batch's keys are compared with
-// the K-th; the few that beat it are appended, through LDS, to the lanes past K, and a full
-// wave (or the end) is sorted again.  The first batch starts from the K-th best of its 64
-// lane maxima: K of the row's columns reach it, so no other column below it can be chosen.
-// So a row costs a compare per column and a handful of wave sorts, against an insertion
-// into a sorted list per column and K wave-wide maxima (700 columns, K = 16, 11,200 rows:
-// 55 -> 25 us; 1,024 columns, K = 8, 2,048 rows: 15 -> 12 us).
+// one per lane, sorted (packed keys, lane r: the r-th).  Columns are compared with a floor
+// that K columns are known to reach; the few that reach it are appended, through LDS, to
+// the lanes past K, and a full wave (or the end) is sorted again.  The floor is the K-th
+// key held or, in a batch with more survivors than there are lanes to append to (the
+// first, and every batch of a row that rises), the K-th best of its 64 lane maxima: K of
+// the batch's columns reach it.  So a row costs a maximum per column, a compare or two
+// where some column survives and a handful of wave sorts, however its scores are ordered,
+// against an insertion into a sorted list per column and K wave-wide maxima.
+// Measured against that form (per call): 8,192 causal rows of up to 8,192 columns, k = 8,
+// 128 -> 33 us, rising rows 128 -> 29, falling ones 37 -> 22; 2,048 rows of up to 1,024,
+// k = 8, 13.3 -> 9.2 us (the launch), k = 32, 54 -> 9.3.  A floor for the first batch only
+// took 48, 228 and 39 us on the first three.
 // GUMBEL: candidates are ranked by score + Gumbel noise; sel reports the raw
 // score of each chosen chunk (read back from the matrix).
 template <bool GUMBEL>
@@ -118,12 +123,16 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
   const int64_t t = row % nQ;
   const int64_t lim = causal ? (t < nC ? t : nC) : nC;
   const float* sr = scores + row * nC;
-  uint64_t best = 0;    // lane r < K: the r-th best key so far (0: none)
-  uint64_t floor_ = 0;  // keys below this are out
-  int held = 0;         // keys appended past lane K
-  auto kth = [&](uint64_t k) {
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(k >> 32), K - 1) << 32) |
-           (uint32_t)__builtin_amdgcn_readlane((int)k, K - 1);
+  uint64_t best = 0;       // lane r < K: the r-th best key so far (0: none)
+  uint64_t last = 0;       // the K-th of them
+  uint32_t reached = 0;    // the highest score (order bits) that K columns so far are known to reach; 0: none
+  float floor_ = -kMaxFloat;  // columns below this are out
+  int held = 0;            // keys appended past lane K
+  auto raise = [&](uint32_t u) {
+    if (u > reached) {
+      reached = u;
+      floor_ = fmaxf(floor_, order_score(u));
+    }
   };
   auto flush = [&]() {
     wave_lds_order();  // other lanes appended the keys ...
@@ -131,7 +140,9 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
     wave_lds_order();  // ... and the next ones are appended after this read
     best = wave_sort_desc(lane < K ? best : appended);
     held = 0;
-    floor_ = max(floor_, kth(best));
+    last = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(best >> 32), K - 1) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)best, K - 1);
+    raise((uint32_t)(last >> 32));
   };
   // kTB scores per lane are loaded before they are used.  With noise a lane takes four
   // consecutive columns at a time (one generator call), else every 64th.
@@ -156,35 +167,43 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
         }
       }
     }
-    uint64_t key[kTB], top = 0;
+    // the K columns that reach the floor came before this batch: a tie with it is lost
+    if (reached != 0) floor_ = order_score(reached + 1);
+    auto lane_max = [&]() {
+      float x = v[0];
+#pragma unroll
+      for (int m = 1; m < kTB; ++m) x = fmaxf(x, v[m]);
+      return x;
+    };
+    float top = lane_max();
+    if (__ballot(top >= floor_) == 0) continue;
+    if (__ballot(top > kMaxFloat) != 0) {  // infinities are no candidates (nor are NaN, which reach no floor)
+#pragma unroll
+      for (int m = 0; m < kTB; ++m) v[m] = v[m] > kMaxFloat ? -INFINITY : v[m];
+      top = lane_max();
+    }
+    int total = 0;
+#pragma unroll
+    for (int m = 0; m < kTB; ++m) total += __popcll(__ballot(v[m] >= floor_));
+    if (total > 64 - K) {
+      const uint32_t u = wave_sort_desc(top >= floor_ ? order_bits(top) : 0u);
+      raise((uint32_t)__builtin_amdgcn_readlane((int)u, K - 1));
+    }
 #pragma unroll
     for (int m = 0; m < kTB; ++m) {
-      const int64_t j = col(j0, m);
-      key[m] = __builtin_isfinite(v[m]) ? pack_key(v[m], (int)j) : 0;  // columns past the row read -inf
-      top = max(top, key[m]);
-    }
-    if (j0 == 0) {
-      top = wave_sort_desc(top);
-      if (!GUMBEL && lim <= 64) {  // one column per lane: that was all
-        best = top;
-        break;
-      }
-      floor_ = kth(top);
-    }
-#pragma unroll
-    for (int m = 0; m < kTB; ++m) {
-      // the floor's own key is a candidate of the first batch only (later floors are
-      // the K-th key already held, whose chunk does not come again)
-      bool in = key[m] >= floor_ && key[m] != 0;
+      bool in = v[m] >= floor_;
+      if (__ballot(in) == 0) continue;
+      const uint64_t key = pack_key(v[m], (int)col(j0, m));
+      in = in && key > last;
       uint64_t mask = __ballot(in);
       while (mask != 0) {
         const int at = held + lanes_below(mask);
         const bool fits = in && K + at < 64;
-        if (fits) sKey[wave][K + at] = key[m];
+        if (fits) sKey[wave][K + at] = key;
         held = min(held + __popcll(mask), 64 - K);
         if (held < 64 - K) break;
         flush();
-        in = in && !fits && key[m] >= floor_;
+        in = in && !fits && key > last;
         mask = __ballot(in);
       }
     }

@@ -33,7 +33,6 @@ template <typename T> struct SelMax;
 template <> struct SelMax<__bf16> { static constexpr int kCh = 8; };  // D <= 512 in registers
 template <> struct SelMax<float> { static constexpr int kCh = 4; };   // D <= 256
 constexpr int kSelThreads = 256;
-constexpr float kMaxFloat = 3.402823466e38f;  // the largest finite score
 constexpr int kSelWaves = kSelThreads / 64;
 static_assert(kSelWaves * 32 == kSelRows, "one 32-row column block per wave");
 

@@ -351,3 +351,47 @@ def test_topk_adversarial_rows(dev, mode, nC, k):
     ref_i, ref_s = og.topk(r.astype(np.float64), k)
     np.testing.assert_array_equal(idx.cpu().numpy(), ref_i)
     np.testing.assert_array_equal(host64(sel), ref_s)
+
+
+@pytest.mark.parametrize("nC,k", [(1023, 8), (5000, 1), (5000, 8), (5000, 31), (5000, 32)])
+def test_topk_rows_in_batches(dev, nC, k):
+    """Rows whose batches of 1,024 columns each hold more survivors than fit, none, or ties with
+    what earlier batches hold: stairs up and down, saw teeth, plateaus of the lowest and highest
+    finite value, a rise among infinities."""
+    import torch
+    from oracle import gca as og
+    from paper_2410_01651_amd import gca
+    j = np.arange(nC)
+    big = np.finfo(np.float32).max
+    rows = [j, -j, j // 100, -(j // 100), j % 1024, -(j % 1000), np.full(nC, -big), np.where(j % 3 == 0, big, 0.0),
+            np.where(j % 2 == 0, np.inf, j), np.where(j < nC - 3, -np.inf, -1.0), np.where(j % 5 == 0, np.nan, j // 7),
+            np.where(j % 64 == 5, -0.0, 0.0)]
+    r = np.stack(rows).astype(np.float32).reshape(len(rows), 1, 1, nC)
+    idx, sel = gca.topk(gca.problem(len(rows), 1, nC, k, D=64, mode="decode"), torch.from_numpy(r).to(dev))
+    ref_i, ref_s = og.topk(r.astype(np.float64), k)
+    np.testing.assert_array_equal(idx.cpu().numpy(), ref_i)
+    np.testing.assert_array_equal(host64(sel), ref_s)
+
+
+def test_topk_time_does_not_depend_on_the_order_of_scores(dev):
+    """Rising rows (recency) cost about what random ones do (a floor for a row's first batch
+    alone made them 4.8 times as long)."""
+    import torch
+    from paper_2410_01651_amd import gca
+    nC = 8192
+    x = torch.randn(64, 1, 1, nC, generator=torch.Generator(device=dev).manual_seed(1), device=dev)
+    p = gca.problem(64, 1, nC, 8, D=64, mode="decode")
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+
+    def best(s):
+        idx, sel = gca.topk(p, s)
+        t = []
+        for _ in range(5):
+            a.record()
+            for _ in range(50):
+                gca.topk(p, s, idx=idx, sel=sel)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+    assert best(x.sort(-1).values.contiguous()) <= 2.0 * best(x)
