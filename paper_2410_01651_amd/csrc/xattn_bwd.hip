@@ -70,31 +70,41 @@ struct LmkShared {
 
 // ----------------------------------- fusion weights and inverse index ----
 
-// One launch prepares the backward.  Workgroup g of a (batch, retrieval head) slice
+// An entry (t, s) is listed under chunk idx[t, s] when row t feeds a query chunk that
+// exists (causal: t + 1 < nQ).  Each list ends up ascending by (t, s): an entry's
+// position is the number of smaller entries in its list (entries are distinct), so the
+// order does not depend on the order of collection.  Two forms:
+//
+// Slices of up to kPrepEntries entries, and decode (one landmark row): one launch.
+// Workgroup g of a (batch, retrieval head) slice
 //  - writes the fusion weights (Eq. 2, as the forward computed them) of the g-th `per`
 //    landmark rows;
 //  - builds the inverse index (CSR) of the g-th `per` key chunks: it reads the whole
 //    slice's retrieval lists, counts the entries of earlier chunks (the offset of its
 //    own lists) and collects its own.
-// An entry (t, s) is listed under chunk idx[t, s] when row t feeds a query chunk that
-// exists (causal: t + 1 < nQ).  Each list ends up ascending by (t, s): an entry's
-// position is the number of smaller entries in its list (entries are distinct), so the
-// order does not depend on the order of collection.
-//
 // Every workgroup reads all of its slice's lists (32 KiB at 1,024 chunks, from the L2)
-// instead of a count, a scan, a fill and a sort launch that each wait for the one
-// before: latency is all that bounds this step.  Six launches took 32 us at 64K tokens
-// (2 x 1,024 chunks, k = 8) and 23 us at 2K; this one takes 18 us and 7 us.
+// instead of a launch per step that each wait for the one before: latency is all that
+// bounds this step while slices are short.
+//
+// Longer slices: weights and counts, scan, fill and sort as launches of their own, whose
+// work grows with the entries only (the one launch's reads grow with entries x groups).
+// One slice, k = 8, one launch / its steps as launches: 1,024 chunks 16 / 28 us, 4,000
+// chunks 32 / 34, 4,200 41 / 35, 8,000 58 / 42; k = 32, 1,500 chunks 72 / 86, 2,500 200 /
+// 95.  Where many slices fill the chip the line lies a little lower or higher (16 slices of
+// 4,000 chunks 126 / 131, 64 of 2,000 187 / 206).
 constexpr int kPrepThreads = 256;
 constexpr int kPrepPool = 2048;   // entries collected in LDS; more go through global memory
 constexpr int kPrepMax = 1024;    // most chunks per workgroup
-// Chunks per workgroup: 16, since a causal slice's first chunks have the longest lists
-// (16 of them about 700 entries at 1,024 chunks and k = 8; 64 chunks per workgroup took
-// 46 us there), and more from 4,096 chunks up, so that at most 256 workgroups read
-// each slice (1,024 from 262,144 up).
-inline int prep_chunks(int64_t nKV) {
-  int per = 16;
-  while (per < kPrepMax && nKV > (int64_t)per * 256) per *= 4;
+constexpr int64_t kPrepEntries = 32768;
+// Chunks per workgroup, such that the first group of a causal slice with evenly spread
+// lists fits the pool: chunk j of n is then retrieved about k ln(n / j) times, so the
+// first `per` chunks hold per k (1 + ln(n / per)) entries.  16 are about 660 at 1,024
+// chunks and k = 8 (64 took 46 us there); k = 32 takes 8, 1,500 entries; from 4,096
+// chunks up at most 256 workgroups read a slice, and its kPrepEntries bound the first
+// group by 840.
+inline int prep_chunks(int64_t nKV, int K) {
+  int per = K > 16 ? 8 : 16;
+  while (per < kPrepMax && nKV > (int64_t)per * 256) per *= 2;
   return per;
 }
 // Position of e in an ascending order of list[lo .. hi): the smaller entries.
@@ -247,6 +257,89 @@ __global__ __launch_bounds__(kPrepThreads) void bwd_prep_kernel(const int32_t* _
       row_weight(sE + row, reinterpret_cast<const float*>(sList) + row, K, nKV, e - row, wv, jv);
       ws.w[at0 + e] = wv;
     }
+  }
+}
+
+// The long form.  A slice's counts, then its fill cursors, sit at the start of its part of
+// ws.sorted, which the last launch overwrites.
+__global__ void bwd_prep_clear_kernel(int* __restrict__ sorted, int64_t BHr, int64_t nQ, int K, int64_t nKV) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < BHr * nKV; i += (int64_t)gridDim.x * blockDim.x)
+    sorted[i / nKV * nQ * K + i % nKV] = 0;
+}
+
+__global__ void bwd_prep_count_kernel(const int32_t* __restrict__ idx, const float* __restrict__ sel, BwdWs ws,
+                                      int64_t BHr, int64_t nQ, int K, int64_t nKV, int causal) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= BHr * nQ * K) return;
+  const int64_t row = e / K;
+  float wv;
+  int j;
+  row_weight(idx + row * K, sel + row * K, K, nKV, (int)(e % K), wv, j);
+  ws.w[e] = wv;
+  if (j >= 0 && row % nQ + causal < nQ) atomicAdd(&ws.sorted[row / nQ * nQ * K + j], 1);
+}
+
+// Exclusive scan of one slice's counts: offs[0 .. nKV], and the cursors in their place.
+constexpr int kPrepScan = 1024;
+__global__ __launch_bounds__(kPrepScan) void bwd_prep_scan_kernel(BwdWs ws, int64_t nQ, int K, int64_t nKV) {
+  __shared__ int sWave[kPrepScan / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int* cur = ws.sorted + (int64_t)blockIdx.x * nQ * K;
+  int* off = ws.offs + (int64_t)blockIdx.x * (nKV + 1);
+  int carry = 0;
+  for (int64_t base = 0; base < nKV; base += kPrepScan) {
+    const int64_t i = base + tid;
+    const int v = i < nKV ? cur[i] : 0;
+    int x = v;  // inclusive scan within the wave
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) sWave[wave] = x;
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int w = 0; w < kPrepScan / 64; ++w) {
+      before += w < wave ? sWave[w] : 0;
+      all += sWave[w];
+    }
+    if (i < nKV) {
+      off[i] = carry + before + x - v;
+      cur[i] = carry + before + x - v;
+    }
+    carry += all;
+    __syncthreads();
+  }
+  if (tid == 0) off[nKV] = carry;
+}
+
+__global__ void bwd_prep_fill_kernel(const int32_t* __restrict__ idx, BwdWs ws, int64_t BHr, int64_t nQ, int K,
+                                     int64_t nKV, int causal) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= BHr * nQ * K) return;
+  const int64_t slice = e / (nQ * K), local = e % (nQ * K);  // t * K + s
+  const int j = idx[e];
+  if (j >= 0 && j < nKV && local / K + causal < nQ)
+    ws.unsorted[slice * nQ * K + atomicAdd(&ws.sorted[slice * nQ * K + j], 1)] = (int)local;
+}
+
+// One wave per chunk.
+__global__ __launch_bounds__(256) void bwd_prep_sort_kernel(BwdWs ws, int64_t BHr, int64_t nQ, int K, int64_t nKV) {
+  const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (wv >= BHr * nKV) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t slice = wv / nKV, j = wv % nKV;
+  const int lo = ws.offs[slice * (nKV + 1) + j], hi = ws.offs[slice * (nKV + 1) + j + 1];
+  const int* src = ws.unsorted + slice * nQ * K;
+  int* head = ws.head + wv * kHeadInts;
+  if (lane == 0) {
+    head[0] = lo;
+    head[1] = hi - lo;
+  }
+  for (int i = lo + lane; i < hi; i += 64) {
+    const int e = src[i], rank = prep_rank(src, lo, hi, e);
+    ws.sorted[slice * nQ * K + lo + rank] = e;
+    if (rank < kHeadEntries) head[2 + rank] = e;
   }
 }
 
@@ -1512,11 +1605,26 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
                         float* dlmk_q, float* dlmk_k, hipStream_t st) {
   const int64_t BHr = (int64_t)s.B * s.Hr, BH = (int64_t)s.B * s.H;
   BwdWs& w = p.ws;
-  // (decode has one landmark row: the groups of its past cover it too)
-  const int per = prep_chunks(s.nKV);
-  const int64_t groups = (s.nKV + per - 1) / per;
-  launch_kernel("bwd_prep_kernel", bwd_prep_kernel, dim3((unsigned)(BHr * groups)), dim3(kPrepThreads), 0, st, p.idx,
-                p.sel, w, s.nQ, s.topk, s.nKV, s.causal, per, groups);
+  if (!s.causal || s.nQ * s.topk <= kPrepEntries) {
+    // (decode has one landmark row: the groups of its past cover it too)
+    const int per = prep_chunks(s.nKV, s.topk);
+    const int64_t groups = (s.nKV + per - 1) / per;
+    launch_kernel("bwd_prep_kernel", bwd_prep_kernel, dim3((unsigned)(BHr * groups)), dim3(kPrepThreads), 0, st,
+                  p.idx, p.sel, w, s.nQ, s.topk, s.nKV, s.causal, per, groups);
+  } else {
+    const dim3 ent((unsigned)((BHr * s.nQ * s.topk + 255) / 256)), chunks((unsigned)((BHr * s.nKV + 3) / 4));
+    launch_kernel("bwd_prep_clear_kernel", bwd_prep_clear_kernel,
+                  dim3((unsigned)std::min<int64_t>((BHr * s.nKV + 255) / 256, 4096)), dim3(256), 0, st, w.sorted, BHr,
+                  s.nQ, s.topk, s.nKV);
+    launch_kernel("bwd_prep_count_kernel", bwd_prep_count_kernel, ent, dim3(256), 0, st, p.idx, p.sel, w, BHr, s.nQ,
+                  s.topk, s.nKV, s.causal);
+    launch_kernel("bwd_prep_scan_kernel", bwd_prep_scan_kernel, dim3((unsigned)BHr), dim3(kPrepScan), 0, st, w, s.nQ,
+                  s.topk, s.nKV);
+    launch_kernel("bwd_prep_fill_kernel", bwd_prep_fill_kernel, ent, dim3(256), 0, st, p.idx, w, BHr, s.nQ, s.topk,
+                  s.nKV, s.causal);
+    launch_kernel("bwd_prep_sort_kernel", bwd_prep_sort_kernel, chunks, dim3(256), 0, st, w, BHr, s.nQ, s.topk,
+                  s.nKV);
+  }
   const int64_t nq_work = BH * s.nQ, nk_work = BH * s.nKV;
   // persistent: kWgPerCu workgroups per CU, kPairs chunk streams each
   const int64_t dq_wgs =

@@ -233,8 +233,13 @@ def test_decode_winners_in_one_scan_list(dev, B, nC, k, pw):
     ("causal", 1, 2, 1, 64, False),
     ("causal", 1, 17, 3, 64, False),       # a second group of one chunk
     ("causal", 2, 300, 8, 512, True),      # one group collects more entries than fit in LDS
-    ("causal", 1, 4200, 2, 1024, False),   # 64 chunks per group; landmark rows of two waves
-    ("decode", 1, 70000, 9, 192, False),   # 1,024 chunks per group, one landmark row
+    ("causal", 1, 4200, 2, 1024, False),   # 32 chunks per group; landmark rows of two waves
+    ("decode", 1, 70000, 9, 192, False),   # 512 chunks per group, one landmark row
+    ("causal", 1, 1024, 32, 64, False),    # 8 chunks per group; as many entries as one launch takes
+    ("causal", 1, 1025, 32, 64, False),    # more: a launch per step
+    ("causal", 2, 4200, 8, 64, False),
+    ("causal", 1, 4200, 8, 192, True),     # the same with lists of 4,199 entries
+    ("causal", 1, 16400, 3, 64, False),
 ])
 def test_backward_preparation(dev, mode, Hr, nC, k, D, hot):
     """Fusion weights, inverse lists and landmark gradients against fp64 torch: with dV and
