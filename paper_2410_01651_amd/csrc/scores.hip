@@ -150,7 +150,15 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
   auto col = [&](int64_t j0, int m) -> int64_t {
     return GUMBEL ? j0 + 256 * (m >> 2) + 4 * lane + (m & 3) : j0 + 64 * m + lane;
   };
-  for (int64_t j0 = 0; j0 < lim; j0 += 64 * kTB) {
+  const bool short_row = lim <= 64;  // one column per lane: one sort is all
+  if (short_row) {
+    float v = lane < lim ? sr[lane] : -INFINITY;
+    if constexpr (GUMBEL) {
+      if (lane < lim) v += gumbel_noise(seed, (uint32_t)(row / nQ), (uint32_t)t, (uint32_t)lane);
+    }
+    best = wave_sort_desc(__builtin_isfinite(v) ? pack_key(v, lane) : 0);
+  }
+  for (int64_t j0 = short_row ? lim : 0; j0 < lim; j0 += 64 * kTB) {
     float v[kTB];
 #pragma unroll
     for (int m = 0; m < kTB; ++m) {
