@@ -1416,13 +1416,27 @@ __global__ __launch_bounds__(64) void dsel_kernel(const float* __restrict__ w, c
   if (s < K) dsel[row * K + s] = ws * (dw - tot);
 }
 
-// Weighted sum of gathered landmark rows by one workgroup:
-//   out[x] = scale * sum_u w_u src[row_u][x],  x < D,
-// for the n (row, weight) pairs staged in sRow / sW.  A thread owns a 16-byte
+// Weighted sum of gathered landmark rows by a team of NT threads (a workgroup, or one
+// wave of it):
+//   out[x] = scale * sum_u w_u src[off_u + x],  x < D,
+// for the n (row offset, weight) pairs staged in sOff / sW.  A thread owns a 16-byte
 // column block and a residue class of u (the groups), so every load is an
-// independent 16-byte read and four are in flight; the groups' partial sums are
-// added in a fixed order (deterministic).
+// independent 16-byte read; the groups' partial sums are added in a fixed order
+// (deterministic).  256 threads keep four reads in flight each; 64 threads, with a
+// quarter of the groups, 8 or 16.
 constexpr int kMaxGatherPasses = 8;  // D <= 8192: at most 8 passes of 256 blocks (fp32); one pass of 64 threads
+
+// column blocks per pass and retriever groups
+struct GatherShape {
+  int pass_cols, groups;
+};
+inline GatherShape gather_shape(int D, int elem_bytes, int threads) {
+  const int nb = D / (16 / elem_bytes);
+  GatherShape g;
+  g.pass_cols = nb < threads ? nb : threads;
+  g.groups = threads / g.pass_cols;
+  return g;
+}
 
 template <typename T>
 __device__ __forceinline__ float elem16(const u32x4& r, int m) {
@@ -1430,18 +1444,43 @@ __device__ __forceinline__ float elem16(const u32x4& r, int m) {
   else return __uint_as_float(r[m]);
 }
 
-template <typename T>
-__device__ __forceinline__ void gather_rows(const T* __restrict__ src, int D, const int64_t* sRow, const float* sW,
-                                            int n, float (&acc)[kMaxGatherPasses][16 / sizeof(T)], int pass_cols,
-                                            int groups) {
+// N entries of one thread's residue class from u on; entries past the list add nothing.
+template <int N, typename T>
+__device__ __forceinline__ void gather_batch(const T* __restrict__ src, const int64_t* sOff, const float* sW, int n,
+                                             int u, int step, bool active, float (&acc)[16 / sizeof(T)]) {
   constexpr int V = 16 / sizeof(T);
-  const int tid = threadIdx.x, cb = tid % pass_cols, grp = tid / pass_cols;
-  const int nb = D / V;
-  auto ld = [&](int u, int b) { return *reinterpret_cast<const u32x4*>(src + sRow[u] * D + b * V); };
+  u32x4 f[N];
+  float w[N];
 #pragma unroll
-  for (int pass = 0; pass < kMaxGatherPasses; ++pass) {
-    const int b = pass * pass_cols + cb;
-    if (pass * pass_cols >= nb) break;
+  for (int i = 0; i < N; ++i) {
+    const int at = min(u + i * step, n - 1);
+    f[i] = *reinterpret_cast<const u32x4*>(src + sOff[at]);
+    w[i] = sW[at];
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (active && u + i * step < n)
+#pragma unroll
+      for (int m = 0; m < V; ++m) acc[m] += w[i] * elem16<T>(f[i], m);
+}
+
+template <typename T, int NT, int PASSES>
+__device__ __forceinline__ void gather_rows(const T* __restrict__ src, int D, const int64_t* sOff, const float* sW,
+                                            int n, float (&acc)[PASSES][16 / sizeof(T)], GatherShape gs) {
+  constexpr int V = 16 / sizeof(T);
+  const int tid = threadIdx.x % NT, cb = tid % gs.pass_cols, grp = tid / gs.pass_cols, groups = gs.groups;
+  const int nb = D / V;
+  if constexpr (NT == 64) {
+    static_assert(PASSES == 1, "one wave covers a row");
+    for (int u0 = 0; u0 < n; u0 += 8 * groups)
+      gather_batch<8>(src + cb * V, sOff, sW, n, u0 + grp, groups, grp < groups, acc[0]);
+    return;
+  }
+  auto ld = [&](int u, int b) { return *reinterpret_cast<const u32x4*>(src + sOff[u] + b * V); };
+#pragma unroll
+  for (int pass = 0; pass < PASSES; ++pass) {
+    const int b = pass * gs.pass_cols + cb;
+    if (pass * gs.pass_cols >= nb) break;
     if (grp < groups && b < nb) {
       int u = grp;
       for (; u + 3 * groups < n; u += 4 * groups) {
@@ -1461,29 +1500,35 @@ __device__ __forceinline__ void gather_rows(const T* __restrict__ src, int D, co
   }
 }
 
-template <typename T>
+// LDS written by the team is visible to it.
+template <int NT>
+__device__ __forceinline__ void gather_sync() {
+  if constexpr (NT == 64) wave_lds_order();
+  else __syncthreads();
+}
+
+template <typename T, int NT, int PASSES>
 __device__ __forceinline__ void gather_store(float* __restrict__ out, int D, float scale, float* sAcc,
-                                             float (&acc)[kMaxGatherPasses][16 / sizeof(T)], int pass_cols,
-                                             int groups) {
+                                             float (&acc)[PASSES][16 / sizeof(T)], GatherShape gs) {
   constexpr int V = 16 / sizeof(T);
-  const int tid = threadIdx.x, cb = tid % pass_cols, grp = tid / pass_cols;
+  const int tid = threadIdx.x % NT, cb = tid % gs.pass_cols, grp = tid / gs.pass_cols, groups = gs.groups;
   const int nb = D / V;
 #pragma unroll
-  for (int pass = 0; pass < kMaxGatherPasses; ++pass) {
-    const int b = pass * pass_cols + cb;
-    if (pass * pass_cols >= nb) break;
-    __syncthreads();
+  for (int pass = 0; pass < PASSES; ++pass) {
+    const int b = pass * gs.pass_cols + cb;
+    if (pass * gs.pass_cols >= nb) break;
+    gather_sync<NT>();
     if (grp < groups && b < nb)
 #pragma unroll
-      for (int m = 0; m < V; ++m) sAcc[(grp * pass_cols + cb) * V + m] = acc[pass][m];
-    __syncthreads();
+      for (int m = 0; m < V; ++m) sAcc[(grp * gs.pass_cols + cb) * V + m] = acc[pass][m];
+    gather_sync<NT>();
     if (grp == 0 && b < nb) {
       float r[V];
 #pragma unroll
       for (int m = 0; m < V; ++m) r[m] = sAcc[cb * V + m];
       for (int g = 1; g < groups; ++g)
 #pragma unroll
-        for (int m = 0; m < V; ++m) r[m] += sAcc[(g * pass_cols + cb) * V + m];
+        for (int m = 0; m < V; ++m) r[m] += sAcc[(g * gs.pass_cols + cb) * V + m];
 #pragma unroll
       for (int m = 0; m < V; m += 4)
         store4(out + b * V + m, scale * r[m], scale * r[m + 1], scale * r[m + 2], scale * r[m + 3]);
@@ -1491,26 +1536,10 @@ __device__ __forceinline__ void gather_store(float* __restrict__ out, int D, flo
   }
 }
 
-// Threads per workgroup, column blocks per pass and retriever groups.  One wave where
-// it covers a row: both kernels are a chain of dependent reads per row, so what counts
-// is the rows in flight (16 heads x 700 rows of width 64, k = 16, in workgroups of 256:
-// 46 us for dlmk_q and 51 us for dlmk_k; of 64: 16 us and 19 us).
-struct GatherShape {
-  int threads, pass_cols, groups;
-};
-inline GatherShape gather_shape(int D, int elem_bytes) {
-  const int nb = D / (16 / elem_bytes);
-  GatherShape g;
-  g.threads = nb <= 64 ? 64 : 256;
-  g.pass_cols = nb < g.threads ? nb : g.threads;
-  g.groups = g.threads / g.pass_cols;
-  return g;
-}
-
 // dlmk_q[t] = score_scale * sum_s dsel[t, s] lmk_k[idx[t, s]]
 // The row's dsel (as dsel_kernel computes it, the same summation order) is
 // formed here and written out, so the backward needs no separate dsel launch
-// when the landmark-query gradient is wanted: all 256 threads read the head
+// when the landmark-query gradient is wanted: all threads read the head
 // classes of the dw partials, and the first wave forms dsel.
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void dlmk_q_kernel(const T* __restrict__ lk, const int32_t* __restrict__ idx,
@@ -1518,8 +1547,8 @@ __global__ __launch_bounds__(NT) void dlmk_q_kernel(const T* __restrict__ lk, co
                                                      float* __restrict__ dsel, float* __restrict__ dlq,
                                                      int64_t nQ, int64_t nKV, int D, int K, int H, int Hr,
                                                      int causal, float scale, GatherShape gs) {
-  constexpr int V = 16 / sizeof(T);
-  __shared__ int64_t sRow[32];
+  constexpr int V = 16 / sizeof(T), PASSES = NT == 64 ? 1 : kMaxGatherPasses;
+  __shared__ int64_t sOff[32];
   __shared__ float sW[32];
   __shared__ int sN;
   __shared__ float sAcc[NT * 8];
@@ -1553,51 +1582,130 @@ __global__ __launch_bounds__(NT) void dlmk_q_kernel(const T* __restrict__ lk, co
     const uint64_t mask = __ballot(ok);
     if (ok) {
       const int rk = __popcll(mask & ((1ull << s) - 1));
-      sRow[rk] = bhr * nKV + j;
+      sOff[rk] = (bhr * nKV + j) * D;
       sW[rk] = ds;
     }
     if (s == 0) sN = __popcll(mask);
   }
   __syncthreads();
-  float acc[kMaxGatherPasses][V];
-  for (int q = 0; q < kMaxGatherPasses; ++q)
+  float acc[PASSES][V];
+  for (int q = 0; q < PASSES; ++q)
     for (int m = 0; m < V; ++m) acc[q][m] = 0.f;
-  gather_rows<T>(lk, D, sRow, sW, sN, acc, gs.pass_cols, gs.groups);
-  gather_store<T>(dlq + row * D, D, scale, sAcc, acc, gs.pass_cols, gs.groups);
+  gather_rows<T, NT>(lk, D, sOff, sW, sN, acc, gs);
+  gather_store<T, NT>(dlq + row * D, D, scale, sAcc, acc, gs);
 }
 
 // dlmk_k[j] = score_scale * sum over the rows (t, s) that retrieved j of dsel[t, s] lmk_q[t],
-// in (t, s) order within each group of the list
-template <typename T, int NT>
-__global__ __launch_bounds__(NT) void dlmk_k_kernel(const T* __restrict__ lq, const int* __restrict__ offs,
-                                                     const int* __restrict__ sorted, const float* __restrict__ dsel,
-                                                     float* __restrict__ dlk, int64_t nQ, int64_t nKV, int D, int K,
-                                                     float scale, GatherShape gs) {
+// in (t, s) order within each group of the list, by a team of NT threads.
+template <typename T, int NT, int PASSES>
+__device__ __forceinline__ void dlmk_k_row(const T* __restrict__ lq, const int* __restrict__ sorted,
+                                           const float* __restrict__ dsel, float* __restrict__ dlk, int64_t nQ,
+                                           int D, int K, float scale, int64_t row, uint32_t slice, int lo, int hi,
+                                           int64_t* sOff, float* sW, float* sAcc, GatherShape gs) {
   constexpr int V = 16 / sizeof(T);
-  constexpr int NB = 256;
-  __shared__ int64_t sRow[NB];
-  __shared__ float sW[NB];
-  __shared__ float sAcc[NT * 8];
-  const int64_t wid = blockIdx.x;  // (b, hr, j)
-  const int64_t bhr = wid / nKV, j = wid % nKV;
-  const int* off = offs + bhr * (nKV + 1);
-  const int lo = off[j], hi = off[j + 1];
-  const int* list = sorted + bhr * nQ * K;
-  float acc[kMaxGatherPasses][V];
-  for (int q = 0; q < kMaxGatherPasses; ++q)
+  const int tid = threadIdx.x % NT;
+  const int64_t q0 = slice * nQ;  // the slice's first landmark row
+  float acc[PASSES][V];
+  for (int q = 0; q < PASSES; ++q)
     for (int m = 0; m < V; ++m) acc[q][m] = 0.f;
-  for (int b0 = lo; b0 < hi; b0 += NB) {
-    const int nb = min(NB, hi - b0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < nb; i += NT) {
-      const int e = list[b0 + i];  // t * K + s
-      sRow[i] = bhr * nQ + e / K;
-      sW[i] = dsel[(bhr * nQ) * K + e];
+  for (int b0 = lo; b0 < hi; b0 += NT) {
+    const int nb = min(NT, hi - b0);
+    gather_sync<NT>();
+    if (tid < nb) {
+      const int e = sorted[q0 * K + b0 + tid];  // t * K + s
+      sOff[tid] = (q0 + e / K) * D;
+      sW[tid] = dsel[q0 * K + e];
     }
-    __syncthreads();
-    gather_rows<T>(lq, D, sRow, sW, nb, acc, gs.pass_cols, gs.groups);
+    gather_sync<NT>();
+    gather_rows<T, NT>(lq, D, sOff, sW, nb, acc, gs);
   }
-  gather_store<T>(dlk + wid * D, D, scale, sAcc, acc, gs.pass_cols, gs.groups);
+  gather_store<T, NT>(dlk + row * D, D, scale, sAcc, acc, gs);
+}
+
+// One row (b, hr, j) per workgroup (rows fit 31 bits).
+template <typename T>
+__global__ __launch_bounds__(256) void dlmk_k_kernel(const T* __restrict__ lq, const int* __restrict__ offs,
+                                                     const int* __restrict__ sorted, const float* __restrict__ dsel,
+                                                     float* __restrict__ dlk, int64_t nQ, uint32_t nKV, int D, int K,
+                                                     float scale, GatherShape gs) {
+  __shared__ int64_t sOff[256];
+  __shared__ float sW[256];
+  __shared__ float sAcc[256 * 8];
+  const int64_t row = blockIdx.x;
+  const uint32_t slice = blockIdx.x / nKV;
+  const int* off = offs + row + slice;  // (nKV + 1 offsets per slice)
+  dlmk_k_row<T, 256, kMaxGatherPasses>(lq, sorted, dsel, dlk, nQ, D, K, scale, row, slice, off[0], off[1], sOff, sW,
+                                       sAcc, gs);
+}
+
+// Landmarks of at most 64 column blocks, many rows (dlmk_k_waves): each wave of a
+// workgroup takes a row of its own, except rows with long lists, which the four waves
+// then take together.  The workgroup's rows lie a quarter of all rows apart, shifted
+// against each other, so that the hot chunks of a slice, and the first ones of several
+// slices, fall to different workgroups.
+template <typename T>
+__global__ __launch_bounds__(256, 4) void dlmk_k_rows_kernel(const T* __restrict__ lq, const int* __restrict__ offs,
+                                                          const int* __restrict__ sorted,
+                                                          const float* __restrict__ dsel, float* __restrict__ dlk,
+                                                          uint32_t rows, int64_t nQ, uint32_t nKV, int D, int K,
+                                                          float scale, GatherShape one, GatherShape four) {
+  __shared__ int64_t sOff[256];
+  __shared__ float sW[256];
+  __shared__ float sAcc[256 * 8];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t G = gridDim.x;
+  const int longest = 32 * one.groups;  // of a list that one wave takes
+  uint32_t row[4], slice[4];
+  int lo[4], n[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    uint32_t x = blockIdx.x + 37 * w;
+    while (x >= G) x -= G;
+    row[w] = min(w * G + x, rows - 1);
+    slice[w] = row[w] / nKV;
+    const int* off = offs + row[w] + slice[w];
+    lo[w] = off[0];
+    n[w] = w * G + x < rows ? off[1] - lo[w] : -1;  // -1: no such row
+  }
+  uint32_t own = row[0], own_slice = slice[0];
+  int own_lo = lo[0], own_n = n[0];
+#pragma unroll
+  for (int w = 1; w < 4; ++w)
+    if (wave == w) {
+      own = row[w];
+      own_slice = slice[w];
+      own_lo = lo[w];
+      own_n = n[w];
+    }
+  if (own_n >= 0 && own_n <= longest)
+    dlmk_k_row<T, 64, 1>(lq, sorted, dsel, dlk, nQ, D, K, scale, own, own_slice, own_lo, own_lo + own_n,
+                         sOff + 64 * wave, sW + 64 * wave, sAcc + 512 * wave, one);
+  if (max(max(n[0], n[1]), max(n[2], n[3])) <= longest) return;
+#pragma unroll 1
+  for (int w = 0; w < 4; ++w) {
+    auto pick = [&](auto& a) { return w == 0 ? a[0] : w == 1 ? a[1] : w == 2 ? a[2] : a[3]; };
+    if (pick(n) > longest) {
+      __syncthreads();
+      dlmk_k_row<T, 256, 1>(lq, sorted, dsel, dlk, nQ, D, K, scale, pick(row), pick(slice), pick(lo),
+                            pick(lo) + pick(n), sOff, sW, sAcc, four);
+    }
+  }
+}
+
+// Landmark gradients one wave per row: where a wave covers a row and the rows fill the
+// chip many times over, what counts is the rows in flight; below, a row's own chain of
+// reads and sums, which a workgroup shortens (the more, the wider the row).  A workgroup /
+// a wave per row, bf16, k = 8: dlmk_q 2,048 rows of width 64 9.0 / 4.7 us, of 512 8.4 / 5.4,
+// 11,200 of 64 (k = 16) 46 / 12; 500 rows with 16 heads' classes to add 4.9 / 6.2.  dlmk_k
+// 1,400 rows of width 64 7.9 / 5.0, of 256 6.9 / 7.3; 2,048 of 256 9.6 / 7.7, of 512
+// 10.4 / 11.4; 4,000 of 512 20.4 / 12.5; 11,200 of 64 (k = 16) 50 / 18.  A list of 1,000
+// on one wave took 22 us at width 64 and 96 at 512, on four 11.5 and 36.
+inline bool dlmk_q_waves(int64_t rows, int D, int elem_bytes) {
+  return D * elem_bytes <= 64 * 16 && rows >= 4 * (int64_t)device_cus();
+}
+inline bool dlmk_k_waves(int64_t rows, int D, int elem_bytes) {
+  const int blocks = D * elem_bytes / 16;  // 16-byte column blocks
+  return dlmk_q_waves(rows, D, elem_bytes) && rows * 16 >= blocks * (int64_t)device_cus() * 3;
 }
 
 template <typename T>
@@ -1649,20 +1757,26 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
   else if (k_pairs == 4) kv(bwd_dkdv_kernel<T, false, 4>, 4);
   else if (k_pairs == 2) kv(bwd_dkdv_kernel<T, false, 2>, 2);
   else kv(bwd_dkdv_kernel<T, false, kB16 ? 1 : 2>, kB16 ? 1 : 2);
-  const GatherShape gs = gather_shape(s.D, sizeof(T));
   if (dlmk_q) {
     // dsel is formed inside the landmark-query gradient kernel
-    launch_kernel("dlmk_q_kernel", gs.threads == 64 ? dlmk_q_kernel<T, 64> : dlmk_q_kernel<T, 256>,
-                  dim3((unsigned)(BHr * s.nQ)), dim3(gs.threads), 0, st, (const T*)lmk_k, p.idx, w.w, w.dwp, dsel,
-                  dlmk_q, s.nQ, s.nKV, s.D, s.topk, s.H, s.Hr, s.causal, s.score_scale, gs);
+    const bool waves = dlmk_q_waves(BHr * s.nQ, s.D, sizeof(T));
+    launch_kernel("dlmk_q_kernel", waves ? dlmk_q_kernel<T, 64> : dlmk_q_kernel<T, 256>, dim3((unsigned)(BHr * s.nQ)),
+                  dim3(waves ? 64 : 256), 0, st, (const T*)lmk_k, p.idx, w.w, w.dwp, dsel, dlmk_q, s.nQ, s.nKV, s.D,
+                  s.topk, s.H, s.Hr, s.causal, s.score_scale, gather_shape(s.D, sizeof(T), waves ? 64 : 256));
   } else {
     launch_kernel("dsel_kernel", dsel_kernel, dim3((unsigned)(BHr * s.nQ)), dim3(64), 0, st, w.w, w.dwp, dsel,
                   s.nQ, s.H, s.Hr, s.topk, s.causal);
   }
   if (dlmk_k) {
-    launch_kernel("dlmk_k_kernel", gs.threads == 64 ? dlmk_k_kernel<T, 64> : dlmk_k_kernel<T, 256>,
-                  dim3((unsigned)(BHr * s.nKV)), dim3(gs.threads), 0, st, (const T*)lmk_q, w.offs, w.sorted, dsel,
-                  dlmk_k, s.nQ, s.nKV, s.D, s.topk, s.score_scale, gs);
+    const int64_t rows = BHr * s.nKV;
+    if (dlmk_k_waves(rows, s.D, sizeof(T)))
+      launch_kernel("dlmk_k_kernel", dlmk_k_rows_kernel<T>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st,
+                    (const T*)lmk_q, w.offs, w.sorted, dsel, dlmk_k, (uint32_t)rows, s.nQ, (uint32_t)s.nKV, s.D, s.topk,
+                    s.score_scale, gather_shape(s.D, sizeof(T), 64), gather_shape(s.D, sizeof(T), 256));
+    else
+      launch_kernel("dlmk_k_kernel", dlmk_k_kernel<T>, dim3((unsigned)rows), dim3(256), 0, st, (const T*)lmk_q, w.offs,
+                    w.sorted, dsel, dlmk_k, s.nQ, (uint32_t)s.nKV, s.D, s.topk, s.score_scale,
+                    gather_shape(s.D, sizeof(T), 256));
   }
   return take_launch_error();
 }

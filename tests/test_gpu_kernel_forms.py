@@ -297,6 +297,44 @@ def test_backward_preparation(dev, mode, Hr, nC, k, D, hot):
     assert max_abs_rel(host64(d["dlmk_k"]), glk[None].cpu().numpy()) <= 1e-5
 
 
+@pytest.mark.parametrize("dtype,B,nC,k,D,hot", [
+    ("bf16", 2, 511, 3, 64, False),     # 1,022 rows: a workgroup each
+    ("bf16", 3, 343, 3, 64, False),     # 1,029: a wave each, the last workgroup with one row
+    ("bf16", 1, 2000, 32, 192, False),  # two groups per wave, idle lanes; first chunks' lists on four waves
+    ("bf16", 7, 450, 8, 512, True),     # one group; hot chunks of several slices
+    ("fp32", 9, 347, 4, 256, False),
+    ("fp32", 4, 300, 32, 64, True),
+])
+def test_landmark_gradients_of_many_rows(dev, dtype, B, nC, k, D, hot):
+    """dlmk_q and dlmk_k against fp64 torch from the kernel's own dsel (tolerance: fp32 sums)."""
+    import torch
+    from paper_2410_01651_amd import gca
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device=dev).manual_seed(nC)
+    t = torch.arange(nC, device=dev).view(1, 1, nC, 1)
+    s = torch.arange(k, device=dev).view(1, 1, 1, k)
+    j = s.expand(B, 1, nC, k) if hot else (t * (s + torch.rand(B, 1, nC, k, generator=g, device=dev)) / k).long()
+    ok = (j < t) if hot else (t > s)
+    idx = torch.where(ok, j, -1).to(torch.int32).contiguous()
+    sel = torch.randn(B, 1, nC, k, generator=g, device=dev).masked_fill(idx < 0, float("-inf"))
+    rnd = lambda *a: torch.randn(*a, generator=g, device=dev, dtype=dt)  # noqa: E731
+    q, kk, v, do = (rnd(B, 1, nC * 64, 64) for _ in range(4))
+    lq, lk = rnd(B, 1, nC, D), rnd(B, 1, nC, D)
+    p = gca.problem(B, 1, nC, k, D=D, dtype=dtype)
+    _, lse, _ = gca.grouped_xattn_fwd(p, q, kk, v, idx, sel)
+    d = gca.grouped_xattn_bwd(p, q, kk, v, idx, sel, lse, do, lq, lk)
+    at = idx.long().clamp(min=0) + nC * torch.arange(B, device=dev).view(B, 1, 1, 1)   # rows of [B * nC, D]
+    c = (d["dsel"].double() * (idx >= 0) / D ** 0.5).view(B * nC, k)
+    lq64, lk64 = lq.double().view(B * nC, D), lk.double().view(B * nC, D)
+    glq, glk = torch.zeros_like(lq64), torch.zeros_like(lk64)
+    for e in range(k):
+        a = at.view(B * nC, k)[:, e]
+        glq += c[:, e:e + 1] * lk64[a]
+        glk.index_add_(0, a, c[:, e:e + 1] * lq64)
+    assert max_abs_rel(host64(d["dlmk_q"]), glq.view(B, 1, nC, D).cpu().numpy()) <= 1e-5
+    assert max_abs_rel(host64(d["dlmk_k"]), glk.view(B, 1, nC, D).cpu().numpy()) <= 1e-5
+
+
 @pytest.mark.parametrize("dtype,H,Hr,nC,k,holes,obo,copies", [
     ("bf16", 1, 1, 2, 1, False, False, 300),
     ("bf16", 4, 1, 16, 8, True, True, 9),       # alone: four wave pairs per item
