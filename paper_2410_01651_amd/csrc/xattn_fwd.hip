@@ -771,6 +771,7 @@ __global__ __launch_bounds__(64, 2) void xattn_fwd_wave_kernel(FwdParams p) {
     sb0 = zero16();
     sb1 = zero16();
     wait_tiles<0>();  // this item's keys
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the last item's values have been read: their tile is free
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(qa[i]), "+v"(qb[i]));
     read_k();
