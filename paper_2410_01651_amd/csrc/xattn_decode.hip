@@ -59,8 +59,12 @@ struct DecParams {
 template <typename T, int SP>
 constexpr bool kB16Sp1 = std::is_same<T, __bf16>::value && SP == 1;
 
+// waves per SIMD to compile for (1: as many registers as a workgroup can have)
+template <typename T, int KM, int SP>
+constexpr int kDecWavesPerSimd = KM == 32 ? 1 : kB16Sp1<T, SP> ? 4 : 2;
+
 template <typename T, bool OBO, bool MERGE, int KM, int SP>
-__global__ __launch_bounds__(kDecThreads, (kB16Sp1<T, SP> ? 4 : 2)) void xattn_decode_kernel(DecParams p) {
+__global__ __launch_bounds__(kDecThreads, (kDecWavesPerSimd<T, KM, SP>)) void xattn_decode_kernel(DecParams p) {
   constexpr int TILE = kS * kD;
   constexpr bool kB16 = std::is_same<T, __bf16>::value;
   constexpr int kPerRound = kDecPairs * SP;
@@ -359,7 +363,8 @@ hipError_t launch_dec_sp(const Shape& s, const DecParams& p, hipStream_t st) {
     else if (s.topk <= 16)
       launch_kernel("xattn_decode_kernel", xattn_decode_kernel<T, OBO, true, 16, SP>, grid, block, 0, st, p);
     else
-      launch_kernel("xattn_decode_kernel", xattn_decode_kernel<T, OBO, true, 32, SP>, grid, block, 0, st, p);
+      launch_kernel("xattn_decode_kernel", xattn_decode_kernel<T, OBO, true, 32, std::is_same<T, __bf16>::value ? 2 : 1>,
+                    grid, block, 0, st, p);
   } else {
     launch_kernel("xattn_decode_kernel", xattn_decode_kernel<T, OBO, false, 8, SP>, grid, block, 0, st, p);
   }
@@ -371,6 +376,9 @@ hipError_t launch_dec_sp(const Shape& s, const DecParams& p, hipStream_t st) {
 // workgroup per CU has; larger grids run two workgroups per CU with one slot each
 // (64 KiB, 128 registers), so that one's merge and copies run beside the other's
 // products: 512 items (32 sequences x 16 heads, 1,000 chunks) 29.5 -> 20.8 us.
+// A merge for k > 16 needs 248 registers (its lists go to scratch memory at 128, and wherever
+// a second wave per SIMD is asked for: 4 x 1,000 chunks, k = 32, 76 -> 160 us), which leave
+// one workgroup per CU: it keeps two slots.
 template <typename T, bool OBO>
 hipError_t launch_dec_t(const Shape& s, const DecParams& p, hipStream_t st) {
   if constexpr (std::is_same<T, __bf16>::value) {
