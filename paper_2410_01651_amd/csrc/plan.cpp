@@ -32,15 +32,19 @@ int device_cus() {
 
 namespace {
 constexpr int64_t kScanTarget = 256, kScanWaves = 4;
+// Fewest keys per wave.  One group of 8 spreads a short past over the chip; for k > 16 the
+// merge of the many long lists this leaves costs more than the scan gains (k = 32, 3,000
+// chunks: scan 14 -> 4 us, attention 81 -> 119; with 64 keys both as before).
+int64_t scan_floor(const Shape& s) { return s.topk > 16 ? 64 : 8; }
 }
 
 DecodePlan decode_plan(const Shape& s) {
-  // about 256 scan workgroups in all, every wave at least one group of 8 keys
+  // about 256 scan workgroups in all, every wave at least scan_floor keys
   const int64_t rows = (int64_t)s.B * s.Hr;
   int64_t wgs = kScanTarget / rows;
   if (wgs < 1) wgs = 1;
   int64_t pw = (s.nKV + wgs * kScanWaves - 1) / (wgs * kScanWaves);
-  pw = (pw + 7) & ~int64_t(7);
+  pw = std::max((pw + 7) & ~int64_t(7), scan_floor(s));
   DecodePlan p;
   p.pw = pw;
   p.wgs = ((s.nKV + pw - 1) / pw + kScanWaves - 1) / kScanWaves;
@@ -54,8 +58,8 @@ DecodePlan decode_plan(const Shape& s) {
 size_t decode_workspace(const Shape& s) {
   const int64_t rows = (int64_t)s.B * s.Hr;
   const int64_t most = rows < kScanTarget ? kScanTarget / rows : 1;  // workgroups per row
-  // a workgroup's waves take 8 chunks or more each
-  const int64_t wgs = std::min(most, (s.nKV + 8 * kScanWaves - 1) / (8 * kScanWaves));
+  const int64_t least = kScanWaves * scan_floor(s);  // chunks of a workgroup but the last
+  const int64_t wgs = std::min(most, (s.nKV + least - 1) / least);
   const size_t n = (size_t)(rows * wgs * kScanWaves) * s.topk;
   return align256(n * sizeof(float)) + align256(n * sizeof(int));
 }

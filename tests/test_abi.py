@@ -71,14 +71,15 @@ def test_workspace_sizes(gca):
     assert gca.workspace_size(p, 7) == 0
 
 
+@pytest.mark.parametrize("topk", [8, 32])
 @pytest.mark.parametrize("rows", [1, 2, 3, 4, 8, 12, 32, 64, 200, 257, 1000])
-def test_decode_workspace_never_falls_as_the_past_grows(gca, rows):
+def test_decode_workspace_never_falls_as_the_past_grows(gca, rows, topk):
     """A program that decodes up to a longest past keeps the workspace sized for that past."""
     last = 0
     pasts = sorted(set(range(1, 400)) | {n + d for e in range(4, 19) for n in (1 << e, 3 << (e - 1)) for d in (0, 1, 8)}
                    | set(range(1000, 40000, 97)))
     for n in pasts:
-        size = gca.workspace_size(gca.problem(rows, 1, n, 8, mode="decode"), gca.OP_FORWARD)
+        size = gca.workspace_size(gca.problem(rows, 1, n, topk, mode="decode"), gca.OP_FORWARD)
         assert size > 0 and size >= last, (n, size, last)
         last = size
 

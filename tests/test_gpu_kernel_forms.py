@@ -197,8 +197,8 @@ def test_decode_large_batch_equals_small(dev, B, H, nC, k, obo):
                 assert max_abs_rel(host64(a), host64(b)) <= tol, n
 
 
-@pytest.mark.parametrize("B,nC,k,pw", [(4, 8192, 14, 32), (4, 8192, 18, 32), (4, 8192, 27, 32), (4, 8000, 32, 32),
-                                       (18, 896, 10, 16), (11, 2200, 22, 24), (2, 1000, 9, 8)])
+@pytest.mark.parametrize("B,nC,k,pw", [(4, 8192, 14, 32), (4, 16384, 18, 64), (4, 16384, 27, 64), (4, 16000, 32, 64),
+                                       (18, 896, 10, 16), (11, 5888, 22, 64), (2, 1000, 9, 8)])
 def test_decode_winners_in_one_scan_list(dev, B, nC, k, pw):
     """Most of a row's best k in the scan's first list (chunks c < 4 pw with c mod 32 < 8, pw
     chunks per list), and list counts whose entries leave the merge's last step of 64 lanes
