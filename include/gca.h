@@ -193,7 +193,7 @@ gca_status gca_grouped_xattn_bwd(const gca_problem* p, const void* q, const void
  * are required (the backward needs them), lse and w may be NULL.  In CAUSAL mode
  * the score matrix is written to the workspace and then selected, or, for long
  * sequences or with GCA_FLAG_FUSED_TOPK, scored and selected without it (landmarks
- * wider than 512 columns, 256 in fp32, then use `out` as scratch until the attention
+ * wider than 512 columns, 256 in fp32, may then use `out` as scratch until the attention
  * writes it, unless it overlaps another argument).  In DECODE mode the past landmark keys are scanned in parallel ranges that
  * each leave their best k in the workspace; the attention kernel merges them
  * into idx/sel (the exact top-k) before attending.

@@ -77,7 +77,13 @@ SelectPlan select_plan(const Shape& s) {
   // to each lane's best-16 list at most; wider ones are staged through LDS in tiles of
   // kWideTile keys
   const bool wide = s.bf16 ? s.D > 512 : s.D > 256;
-  p.split = s.causal && s.topk <= 16;
+  // Wide landmarks of few chunks stay with the one-pass form: their triangle is too few
+  // tiles to split, and clearing and merging take two more launches.  A forward of width
+  // 1,024, k = 4, one-pass / split: 1 x 64 chunks 31 / 48 us, 1 x 128 52 / 71, 1 x 200 80 /
+  // 84, 1 x 256 92 / 88; 8 x 64 94 / 104, 8 x 128 189 / 196, 8 x 160 235 / 230, 8 x 256
+  // 363 / 331; k = 16 and fp32 alike.
+  const int64_t rows = (int64_t)s.B * s.Hr * s.nQ;
+  p.split = s.causal && s.topk <= 16 && (!wide || s.nKV >= 256 || (s.nKV > 128 && rows >= 1024));
   p.blocks = (s.nQ + kSelRows - 1) / kSelRows;
   p.tile = wide ? kWideTile : kSelTile;
   p.tiles = (s.nKV + p.tile - 1) / p.tile;

@@ -108,6 +108,8 @@ def test_forward_streams_ending_in_empty_chunks(dev, B, H, nC, first_empty):
     ("bf16", 640, 1100, 16, True),
     ("bf16", 576, 9100, 5, False),       # several parts per class
     ("fp32", 320, 700, 8, True),
+    ("bf16", 1024, 257, 8, False),       # a third row block of one row and a ragged third key tile
+    ("bf16", 576, 255, 8, False),        # the most chunks of few rows that stay with the one-pass form
 ])
 def test_wide_select_equals_score_matrix(dev, dtype, D, nC, k, gumbel):
     """Selection without the matrix for landmarks too wide for registers (its lists in the
@@ -136,6 +138,7 @@ def test_wide_select_equals_score_matrix(dev, dtype, D, nC, k, gumbel):
 @pytest.mark.parametrize("dtype,D,nC,k,gumbel", [
     ("bf16", 64, 300, 8, False), ("bf16", 512, 150, 16, True), ("fp32", 256, 200, 5, False),   # queries in registers
     ("bf16", 576, 300, 8, False), ("bf16", 1024, 150, 16, True), ("fp32", 320, 200, 5, False),  # both through LDS
+    ("bf16", 1024, 290, 16, True), ("fp32", 320, 260, 5, False),
 ])
 def test_select_without_matrix_takes_finite_scores_only(dev, dtype, D, nC, k, gumbel):
     """Scores that overflow to +inf and -inf are no candidates, in rows with and without k finite
@@ -170,6 +173,41 @@ def test_select_without_matrix_takes_finite_scores_only(dev, dtype, D, nC, k, gu
         assert np.isfinite(s[i >= 0]).all(), name
         np.testing.assert_array_equal(i, got["matrix"][0])
         np.testing.assert_array_equal(s, got["matrix"][1])
+
+
+def _kernels(fn):
+    """Names of the kernels that fn launches, in order."""
+    import ctypes
+    import torch
+    from paper_2410_01651_amd import gca
+    hip = ctypes.CDLL("libamdhip64.so")
+    ev = (ctypes.c_void_p * 32)()
+    for i in range(32):
+        assert hip.hipEventCreate(ctypes.byref(ev, i * ctypes.sizeof(ctypes.c_void_p))) == 0
+    try:
+        torch.cuda.synchronize()
+        gca.profile_arm(ev, 32)
+        fn()
+        torch.cuda.synchronize()
+        return gca.profile_record()
+    finally:
+        gca.profile_arm(None, 0)
+        for i in range(32):
+            hip.hipEventDestroy(ctypes.c_void_p(ev[i]))
+
+
+@pytest.mark.parametrize("B,nC,split", [(1, 64, False), (1, 255, False), (1, 256, True), (8, 128, False),
+                                        (7, 146, False), (8, 129, True)])
+def test_wide_select_splits_many_chunks_only(dev, B, nC, split):
+    """Few chunks are too few tiles for the split selection to pay for its two extra launches."""
+    import torch
+    from paper_2410_01651_amd import gca
+    p = gca.problem(B, 1, nC, 4, D=1024, flags=gca.FLAG_FUSED_TOPK)
+    lq, lk = (torch.zeros(B, 1, nC, 1024, device=dev, dtype=torch.bfloat16) for _ in range(2))
+    q, kk, v = (torch.zeros(B, 1, nC * 64, 64, device=dev, dtype=torch.bfloat16) for _ in range(3))
+    names = _kernels(lambda: gca.forward(p, lq, lk, q, kk, v))
+    assert ("select_wide_kernel" in names) == split
+    assert ("fused_select_kernel" in names) != split
 
 
 @pytest.mark.parametrize("B,H,nC,k,obo", [(65, 4, 40, 8, False), (20, 13, 9, 12, True), (130, 2, 33, 32, False),
