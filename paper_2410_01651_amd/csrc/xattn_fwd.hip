@@ -830,8 +830,10 @@ hipError_t launch_xattn_fwd(const Shape& s, const void* q, const void* k, const 
   // (two workgroups per CU in bf16, one in fp32): the kernels below would take a chunk's
   // slots one after another on a chip that is mostly idle; that one takes them side by
   // side.  444 chunks, k = 8, bf16: 15.7 -> 12.0 us; 16 in fp32, k = 2: 14.2 -> 10.4 us.
+  // One slot (k = 1) leaves nothing to take side by side: 504 chunks in bf16 7.1 us there,
+  // 6.0 below, 252 in fp32 11.2 and 10.3.
   const int64_t items = (int64_t)s.B * s.H * s.nQ;
-  if (!s.causal || (s.Sq == kS && items <= (s.bf16 ? 2 : 1) * (int64_t)device_cus()))
+  if (!s.causal || (s.Sq == kS && s.topk > 1 && items <= (s.bf16 ? 2 : 1) * (int64_t)device_cus()))
     return launch_xattn_decode(s, nullptr, nullptr, q, k, v, const_cast<int32_t*>(idx), const_cast<float*>(sel), out,
                                lse, w, nullptr, nullptr, stream);
   FwdParams p;

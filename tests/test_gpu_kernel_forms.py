@@ -380,6 +380,7 @@ def test_landmark_gradients_of_many_rows(dev, dtype, B, nC, k, D, hot):
     ("bf16", 3, 1, 30, 12, False, False, 12),
     ("fp32", 1, 1, 16, 2, True, False, 40),
     ("fp32", 4, 4, 60, 11, True, True, 5),
+    ("bf16", 12, 12, 42, 1, False, True, 4),
 ])
 def test_few_items_equal_many(dev, dtype, H, Hr, nC, k, holes, obo, copies):
     """A problem of few items (several wave pairs per query or key chunk) against the same
@@ -406,6 +407,19 @@ def test_few_items_equal_many(dev, dtype, H, Hr, nC, k, holes, obo, copies):
         ref = host64(few[n])
         for b in (0, copies - 1):
             assert max_abs_rel(host64(many[n][b:b + 1]), ref) <= tol, (n, b)
+
+
+def test_one_slot_takes_the_per_chunk_forward(dev):
+    """k = 1 leaves nothing for several wave pairs to take side by side."""
+    import torch
+    from paper_2410_01651_amd import gca
+    for dtype, dt in (("bf16", torch.bfloat16), ("fp32", torch.float32)):
+        q, kk, v = (torch.zeros(1, 4, 40 * 64, 64, device=dev, dtype=dt) for _ in range(3))
+        for k, name in ((1, "xattn_fwd_kernel"), (2, "xattn_decode_kernel")):
+            idx = torch.zeros(1, 1, 40, k, device=dev, dtype=torch.int32)
+            sel = torch.zeros(1, 1, 40, k, device=dev)
+            p = gca.problem(1, 4, 40, k, dtype=dtype)
+            assert _kernels(lambda: gca.grouped_xattn_fwd(p, q, kk, v, idx, sel)) == [name]
 
 
 @pytest.mark.parametrize("mode", ["causal", "decode"])
