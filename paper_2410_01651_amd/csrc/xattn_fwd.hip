@@ -81,18 +81,18 @@ __device__ __forceinline__ RowMeta load_row_meta(const FwdParams& p, int64_t row
   return m;
 }
 
-template <typename T, bool OBO, bool XR>
-__global__ __launch_bounds__(kThreads, (sizeof(T) == 4 && !XR ? 2 : kWgPerCu)) void xattn_fwd_kernel(FwdParams p) {
+template <typename T, bool OBO, bool XR, bool ONE>
+__global__ __launch_bounds__(kThreads, (ONE ? 2 : kWgPerCu)) void xattn_fwd_kernel(FwdParams p) {
+  static_assert(!ONE || (sizeof(T) == 4 && !XR), "one ring slot is for fp32 without the LMK row");
   constexpr int TILE = kS * kD;
   constexpr int SQ = XR ? kS + 1 : kS;  // query rows per chunk
   static_assert(kPairs == 1, "the LMK row exchange assumes one pair per workgroup");
   __shared__ __attribute__((aligned(16))) LmkShared<T> sX[1];  // used with XR only
-  // In fp32 a tile pair is 32 KiB and a round's products take five times as long as in
-  // bf16, so a second ring slot hides little and costs the second wave per SIMD (two
-  // workgroups per CU instead of four): one slot, copied between rounds while the CU's
-  // other workgroups compute (2,000 chunks, k = 8: 182 -> 165 us; 8,000: 666 -> 609).  With the LMK row the registers of a second wave
-  // are not there either way.
-  constexpr bool ONE = sizeof(T) == 4 && !XR;
+  // ONE (fp32 without the LMK row, whose registers leave one wave per SIMD anyway): one
+  // ring slot, copied between rounds while the CU's other workgroups compute.  In fp32 a
+  // tile pair is 32 KiB and a round's products take five times as long as in bf16, so a
+  // second slot hides little and costs the second wave per SIMD (two workgroups per CU
+  // instead of four).  See fp32_two_slots for where that pays.
   __shared__ __attribute__((aligned(16))) T ring[kPairs * (ONE ? 1 : 2) * 2 * TILE];  // pair p: slots 2p, 2p+1 (K and V tiles)
   __shared__ int sJ[kPairs][2][32];     // [pair][chunk parity][slot]: chunk index or -1
   __shared__ int sSlot[kPairs][2][32];  // compacted lists of the valid slots: slot, chunk, weight
@@ -821,6 +821,19 @@ __global__ __launch_bounds__(64, 2) void xattn_fwd_wave_kernel(FwdParams p) {
   wait_tiles<0>();  // no copy outlives the workgroup's LDS
 }
 
+// Ring slots of the fp32 pair form (without the LMK row): two where the items fill whole
+// passes of two workgroups per CU but not of four.  A pass of the two-slot form takes
+// 43 us at k = 8 for up to two items per CU; the one-slot form's passes of four take 35,
+// 73, 76 and 78 us for 1 to 4 items per CU (two workgroups on a CU share SIMDs).
+// Two slots / one, k = 8: 504 items (2 per CU) 46 / 74 us, 516 53 / 76, 600 84 / 76, 1,020
+// (4) 87 / 80, 1,032 88 / 113, 1,056 97 / 114, 1,116 123 / 114, 1,284 124 / 144, 1,536 (6)
+// 128 / 146, 1,548 163 / 149, 2,052 200 / 178, 2,340 (10) 206 / 214, 2,568 242 / 221, 8,000
+// 666 / 609; k = 2 and 16 alike (2,340 items, k = 2: 68 / 64).
+inline bool fp32_two_slots(int64_t items) {
+  const int64_t cus = device_cus(), per_cu = (items + cus - 1) / cus;
+  return 8 * items <= 17 * cus || (items > 4 * cus && 4 * items <= 17 * cus) || per_cu == 6 || per_cu == 10;
+}
+
 }  // namespace
 
 hipError_t launch_xattn_fwd(const Shape& s, const void* q, const void* k, const void* v,
@@ -861,11 +874,14 @@ hipError_t launch_xattn_fwd(const Shape& s, const void* q, const void* k, const 
     return take_launch_error();
   }
   if (s.bf16) {
-    if (xr) s.off_by_one ? go(xattn_fwd_kernel<__bf16, true, true>) : go(xattn_fwd_kernel<__bf16, false, true>);
-    else s.off_by_one ? go(xattn_fwd_kernel<__bf16, true, false>) : go(xattn_fwd_kernel<__bf16, false, false>);
+    if (xr) s.off_by_one ? go(xattn_fwd_kernel<__bf16, true, true, false>) : go(xattn_fwd_kernel<__bf16, false, true, false>);
+    else s.off_by_one ? go(xattn_fwd_kernel<__bf16, true, false, false>) : go(xattn_fwd_kernel<__bf16, false, false, false>);
+  } else if (xr) {
+    s.off_by_one ? go(xattn_fwd_kernel<float, true, true, false>) : go(xattn_fwd_kernel<float, false, true, false>);
+  } else if (fp32_two_slots(items)) {
+    s.off_by_one ? go(xattn_fwd_kernel<float, true, false, false>) : go(xattn_fwd_kernel<float, false, false, false>);
   } else {
-    if (xr) s.off_by_one ? go(xattn_fwd_kernel<float, true, true>) : go(xattn_fwd_kernel<float, false, true>);
-    else s.off_by_one ? go(xattn_fwd_kernel<float, true, false>) : go(xattn_fwd_kernel<float, false, false>);
+    s.off_by_one ? go(xattn_fwd_kernel<float, true, false, true>) : go(xattn_fwd_kernel<float, false, false, true>);
   }
   return take_launch_error();
 }

@@ -380,6 +380,8 @@ def test_landmark_gradients_of_many_rows(dev, dtype, B, nC, k, D, hot):
     ("bf16", 3, 1, 30, 12, False, False, 12),
     ("fp32", 1, 1, 16, 2, True, False, 40),
     ("fp32", 4, 4, 60, 11, True, True, 5),
+    ("fp32", 8, 1, 63, 8, True, False, 7),      # 504 and 3,528 items: two ring slots and one in the forward
+    ("fp32", 12, 1, 90, 3, True, True, 4),      # 1,080 (two slots) and 4,320
     ("bf16", 12, 12, 42, 1, False, True, 4),
 ])
 def test_few_items_equal_many(dev, dtype, H, Hr, nC, k, holes, obo, copies):
@@ -420,6 +422,57 @@ def test_one_slot_takes_the_per_chunk_forward(dev):
             sel = torch.zeros(1, 1, 40, k, device=dev)
             p = gca.problem(1, 4, 40, k, dtype=dtype)
             assert _kernels(lambda: gca.grouped_xattn_fwd(p, q, kk, v, idx, sel)) == [name]
+
+
+def _best_ms(fn):
+    """The shortest of five runs of 20 calls in a graph."""
+    import torch
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        fn()
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        for _ in range(20):
+            fn()
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    t = []
+    for _ in range(6):
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b))
+    return min(t[1:])
+
+
+def _cus():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def _fp32_step(dev, items, k, bwd):
+    """Time of the attention forward or the backward of one fp32 head of `items` chunks."""
+    import torch
+    from paper_2410_01651_amd import gca
+    g = torch.Generator(device=dev).manual_seed(items)
+    H, nC = 12, items // 12
+    idx, sel = _lists(np.random.default_rng(k), 1, nC, k, False)
+    ti, ts = (torch.from_numpy(x.reshape(1, 1, nC, k)).to(dev) for x in (idx, sel))
+    q, kk, v, do = (torch.randn(1, H, nC * 64, 64, generator=g, device=dev) for _ in range(4))
+    p = gca.problem(1, H, nC, k, D=64, dtype="fp32")
+    out, lse, w = gca.grouped_xattn_fwd(p, q, kk, v, ti, ts)
+    if not bwd:
+        return _best_ms(lambda: gca.grouped_xattn_fwd(p, q, kk, v, ti, ts, out=out, lse=lse, w=w))
+    ws = gca.workspace(p, gca.OP_BACKWARD)[0]
+    d = gca.grouped_xattn_bwd(p, q, kk, v, ti, ts, lse, do, landmark_grads=False, ws=ws)
+    return _best_ms(lambda: gca.grouped_xattn_bwd(p, q, kk, v, ti, ts, lse, do, landmark_grads=False, ws=ws, grads=d))
+
+
+def test_fp32_forward_time_of_two_items_per_cu(dev):
+    """Two fp32 items per CU take about half of four (0.53; with one ring slot 0.92)."""
+    cus = _cus()
+    assert _fp32_step(dev, 2 * cus // 12 * 12, 8, False) <= 0.75 * _fp32_step(dev, 4 * cus // 12 * 12, 8, False)
 
 
 @pytest.mark.parametrize("mode", ["causal", "decode"])
