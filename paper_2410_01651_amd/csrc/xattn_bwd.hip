@@ -980,14 +980,24 @@ inline int few_pairs(int64_t items, bool bf16) {
   if (items > 2 * cus) return 1;
   return items <= cus || !bf16 ? 4 : 2;
 }
+// For dQ, unless the lists are too short to share out: one pair for k = 1, and for k <= 3
+// from one item per CU (the whole backward at 504 fp32 items, few_pairs' / one pair: k = 1
+// 86 / 72 us, k = 2 97 / 88, k = 3 142 / 127; in bf16 31.5 / 29.9, 37.1 / 34.4, 42.5 / 41.5;
+// at 240 fp32 items k = 1 54 / 51, k = 2 65 / 67, k = 3 79 / 82).
+inline int q_pairs_of(int64_t items, int K, bool bf16) {
+  return K <= (items <= (int64_t)device_cus() ? 1 : 3) ? 1 : few_pairs(items, bf16);
+}
 // The same for dK/dV, whose longest list bounds a causal launch for longer in fp32: 4 up to
-// four items per CU, 2 beyond (start: one pair, two ring slots): 800 items 286 -> 165 us
-// (two pairs 202), 2,000 items 374 -> 343 (four pairs 397), 8,000 items 1,292 -> 1,225.
+// four items per CU, 2 beyond (800 items, k = 8: 202 us with two pairs, 165 with four;
+// 2,000 items 343 / 397; one pair with two ring slots 286 and 374) and for k <= 3, whose
+// lists leave most pairs nothing to do (the whole backward, four pairs / two: k = 1 at 240
+// items 54 / 51 us, 504 86 / 77, 768 99 / 91, 1,020 114 / 100; k = 2 65 / 62, 97 / 95,
+// 130 / 127, 166 / 152; k = 3 79 / 79, 142 / 142, 170 / 166, 207 / 206).
 // In bf16 one pair is as good or better from three items per CU (1,200 items 47 us
 // each way, 6,400 items 148 against 184 us).
-inline int kv_pairs(int64_t items, bool bf16) {
+inline int kv_pairs(int64_t items, int K, bool bf16) {
   if (bf16) return few_pairs(items, bf16);
-  return items <= 4 * (int64_t)device_cus() ? 4 : 2;
+  return K > 3 && items <= 4 * (int64_t)device_cus() ? 4 : 2;
 }
 
 // ---------------------------------------------- key-stationary dK, dV ----
@@ -1742,7 +1752,7 @@ hipError_t launch_bwd_t(const Shape& s, BwdParams& p, float* dsel, const void* l
     launch_kernel("bwd_dq_kernel", kernel, dim3((unsigned)dq_wgs), dim3(kThreads), 0, st, p, nq_work);
   };
   constexpr bool kB16 = sizeof(T) == 2;
-  const int q_pairs = xr ? 1 : few_pairs(nq_work, kB16), k_pairs = xr ? 1 : kv_pairs(nk_work, kB16);
+  const int q_pairs = xr ? 1 : q_pairs_of(nq_work, s.topk, kB16), k_pairs = xr ? 1 : kv_pairs(nk_work, s.topk, kB16);
   if (q_pairs > 1)
     launch_kernel("bwd_dq_kernel", q_pairs == 4 ? bwd_dq_few_kernel<T, 4> : bwd_dq_few_kernel<T, kB16 ? 2 : 4>,
                   dim3((unsigned)nq_work), dim3(128 * q_pairs), 0, st, p);

@@ -382,6 +382,7 @@ def test_landmark_gradients_of_many_rows(dev, dtype, B, nC, k, D, hot):
     ("fp32", 4, 4, 60, 11, True, True, 5),
     ("fp32", 8, 1, 63, 8, True, False, 7),      # 504 and 3,528 items: two ring slots and one in the forward
     ("fp32", 12, 1, 90, 3, True, True, 4),      # 1,080 (two slots) and 4,320
+    ("fp32", 4, 1, 60, 1, True, False, 30),     # one slot per chunk: nothing to share out
     ("bf16", 12, 12, 42, 1, False, True, 4),
 ])
 def test_few_items_equal_many(dev, dtype, H, Hr, nC, k, holes, obo, copies):
@@ -473,6 +474,13 @@ def test_fp32_forward_time_of_two_items_per_cu(dev):
     """Two fp32 items per CU take about half of four (0.53; with one ring slot 0.92)."""
     cus = _cus()
     assert _fp32_step(dev, 2 * cus // 12 * 12, 8, False) <= 0.75 * _fp32_step(dev, 4 * cus // 12 * 12, 8, False)
+
+
+def test_fp32_backward_time_of_one_slot(dev):
+    """Lists of one entry give four wave pairs per chunk nothing to share: two chunks per CU
+    take 0.70 of the time of three (0.86 with four pairs per chunk)."""
+    cus = _cus()
+    assert _fp32_step(dev, 2 * cus // 12 * 12, 1, True) <= 0.79 * _fp32_step(dev, 3 * cus // 12 * 12, 1, True)
 
 
 @pytest.mark.parametrize("mode", ["causal", "decode"])
