@@ -32,10 +32,17 @@ int device_cus() {
 
 namespace {
 constexpr int64_t kScanTarget = 256, kScanWaves = 4;
-// Fewest keys per wave.  One group of 8 spreads a short past over the chip; for k > 16 the
-// merge of the many long lists this leaves costs more than the scan gains (k = 32, 3,000
-// chunks: scan 14 -> 4 us, attention 81 -> 119; with 64 keys both as before).
-int64_t scan_floor(const Shape& s) { return s.topk > 16 ? 64 : 8; }
+// Fewest keys per wave (never more for a longer past: see decode_workspace).  One group of
+// 8 spreads a short past over the chip; for k > 8 merging the longer lists that this leaves
+// can cost more than the scan gains.  64 / 8 keys, us a call: k = 32, 3,000 chunks 96 / 122;
+// k = 12, per-head landmarks (width 64), 256 chunks 28 / 30, 768 30 / 33, 2,000 31 / 33,
+// 6,000 34 / 34; k = 9, width 256, 128 chunks 25.7 / 26.9, 200 29.1 / 26.5; width 512, 64
+// chunks 24.3 / 26.6, 100 26.8 / 26.5.  k <= 8 takes the same time or less with 8.
+int64_t scan_floor(const Shape& s) {
+  const int64_t key = (int64_t)s.D * (s.bf16 ? 2 : 4);
+  const bool cheap = s.D <= 64 || s.nKV * key <= 64 * 1024;  // to scan
+  return s.topk > 16 || (s.topk > 8 && cheap) ? 64 : 8;
+}
 }
 
 DecodePlan decode_plan(const Shape& s) {

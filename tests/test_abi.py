@@ -71,17 +71,28 @@ def test_workspace_sizes(gca):
     assert gca.workspace_size(p, 7) == 0
 
 
-@pytest.mark.parametrize("topk", [8, 32])
+@pytest.mark.parametrize("topk,D", [(8, 64), (12, 64), (12, 256), (16, 1024), (32, 64)])
 @pytest.mark.parametrize("rows", [1, 2, 3, 4, 8, 12, 32, 64, 200, 257, 1000])
-def test_decode_workspace_never_falls_as_the_past_grows(gca, rows, topk):
+def test_decode_workspace_never_falls_as_the_past_grows(gca, rows, topk, D):
     """A program that decodes up to a longest past keeps the workspace sized for that past."""
     last = 0
     pasts = sorted(set(range(1, 400)) | {n + d for e in range(4, 19) for n in (1 << e, 3 << (e - 1)) for d in (0, 1, 8)}
                    | set(range(1000, 40000, 97)))
     for n in pasts:
-        size = gca.workspace_size(gca.problem(rows, 1, n, topk, mode="decode"), gca.OP_FORWARD)
+        size = gca.workspace_size(gca.problem(rows, 1, n, topk, D=D, mode="decode"), gca.OP_FORWARD)
         assert size > 0 and size >= last, (n, size, last)
         last = size
+
+
+@pytest.mark.parametrize("topk,D,n,one", [
+    (9, 64, 256, True), (16, 64, 256, True), (16, 64, 257, False), (12, 256, 128, True), (12, 256, 129, False),
+    (12, 512, 64, True), (12, 512, 65, False), (8, 64, 65, False), (17, 1024, 256, True),
+])
+def test_decode_scan_of_cheap_pasts_leaves_few_lists(gca, topk, D, n, one):
+    """Above k = 8, pasts that cost little to scan are scanned by one workgroup (four lists of
+    at least 64 keys), whose merge is shorter: the workspace is that of a single key."""
+    size = lambda m: gca.workspace_size(gca.problem(1, 1, m, topk, D=D, mode="decode"), gca.OP_FORWARD)  # noqa: E731
+    assert (size(n) == size(1)) == one
 
 
 FAKE = ctypes.c_void_p(1 << 20)   # aligned, never dereferenced: validation fails first

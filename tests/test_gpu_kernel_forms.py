@@ -245,7 +245,7 @@ def test_decode_winners_in_one_scan_list(dev, B, nC, k, pw):
     from oracle import gca as og
     from paper_2410_01651_amd import gca
     rng = np.random.default_rng(nC + k)
-    D = 64
+    D = 256
     val = -rng.integers(1, 256, (B, nC)).astype(np.float32)
     first = np.arange(nC)[(np.arange(nC) < 4 * pw) & (np.arange(nC) % 32 < 8)]
     for b in range(B):
@@ -255,11 +255,11 @@ def test_decode_winners_in_one_scan_list(dev, B, nC, k, pw):
     lk = np.zeros((B, 1, nC, D), np.float32)
     lk[:, 0, :, 3] = val
     lq = np.zeros((B, 1, 1, D), np.float32)
-    lq[..., 3] = 8.0
+    lq[..., 3] = 16.0
     g = torch.Generator(device=dev).manual_seed(nC)
     q = torch.randn(B, 1, 64, 64, generator=g, device=dev, dtype=torch.bfloat16)
     kk, v = (torch.randn(B, 1, nC * 64, 64, generator=g, device=dev, dtype=torch.bfloat16) for _ in range(2))
-    p = gca.problem(B, 1, nC, k, D=D, mode="decode")  # score scale 1/8
+    p = gca.problem(B, 1, nC, k, D=D, mode="decode")  # score scale 1/16
     up = lambda a: torch.from_numpy(a).to(dev).bfloat16()  # noqa: E731
     f = gca.forward(p, up(lq), up(lk), q, kk, v)
     ref_i, ref_s = og.topk(val[:, None, None, :].astype(np.float64), k)
