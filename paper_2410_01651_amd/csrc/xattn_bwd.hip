@@ -980,24 +980,20 @@ inline int few_pairs(int64_t items, bool bf16) {
   if (items > 2 * cus) return 1;
   return items <= cus || !bf16 ? 4 : 2;
 }
-// For dQ, unless the lists are too short to share out: one pair for k = 1, and for k <= 3
-// from one item per CU (the whole backward at 504 fp32 items, few_pairs' / one pair: k = 1
-// 86 / 72 us, k = 2 97 / 88, k = 3 142 / 127; in bf16 31.5 / 29.9, 37.1 / 34.4, 42.5 / 41.5;
-// at 240 fp32 items k = 1 54 / 51, k = 2 65 / 67, k = 3 79 / 82).
-inline int q_pairs_of(int64_t items, int K, bool bf16) {
-  return K <= (items <= (int64_t)device_cus() ? 1 : 3) ? 1 : few_pairs(items, bf16);
-}
+// For dQ, unless lists of one entry (k = 1) leave nothing to share out: the whole backward
+// at 504 items, few_pairs' pairs / one: 86 / 72 us in fp32, 31.5 / 29.9 in bf16; at 240
+// fp32 items 54 / 51.
+inline int q_pairs_of(int64_t items, int K, bool bf16) { return K == 1 ? 1 : few_pairs(items, bf16); }
 // The same for dK/dV, whose longest list bounds a causal launch for longer in fp32: 4 up to
 // four items per CU, 2 beyond (800 items, k = 8: 202 us with two pairs, 165 with four;
-// 2,000 items 343 / 397; one pair with two ring slots 286 and 374) and for k <= 3, whose
-// lists leave most pairs nothing to do (the whole backward, four pairs / two: k = 1 at 240
-// items 54 / 51 us, 504 86 / 77, 768 99 / 91, 1,020 114 / 100; k = 2 65 / 62, 97 / 95,
-// 130 / 127, 166 / 152; k = 3 79 / 79, 142 / 142, 170 / 166, 207 / 206).
+// 2,000 items 343 / 397; one pair with two ring slots 286 and 374) and for k = 1, whose
+// lists leave most pairs nothing to do (the whole backward, four pairs / two: 240 items
+// 54 / 51 us, 504 86 / 77, 768 99 / 91, 1,020 114 / 100).
 // In bf16 one pair is as good or better from three items per CU (1,200 items 47 us
 // each way, 6,400 items 148 against 184 us).
 inline int kv_pairs(int64_t items, int K, bool bf16) {
   if (bf16) return few_pairs(items, bf16);
-  return K > 3 && items <= 4 * (int64_t)device_cus() ? 4 : 2;
+  return K > 1 && items <= 4 * (int64_t)device_cus() ? 4 : 2;
 }
 
 // ---------------------------------------------- key-stationary dK, dV ----
