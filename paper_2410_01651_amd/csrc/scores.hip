@@ -283,12 +283,11 @@ __device__ __forceinline__ float dot_block(const u32x4* v, const f32x8 b, float 
 // descriptor per key group, whose range check zeroes the lanes past the end of
 // the wave's range with no memory access, and run one batch of 8 column blocks
 // ahead of the arithmetic.  The plan spreads any number of keys over about one
-// workgroup per CU, down to one key group per wave where
-// that pays (scan_floor): bound by the key stream for long
-// pasts, by a few round trips for short ones.  16,384 keys of width 768: 18.4 -> 7.8 us
-// against ranges of at least 64 keys per wave (64 workgroups); 32 rows of 1,000 keys of
-// width 1,024: 22.6 -> 14.4 us.  The lists this adds (up to 1,024 per row) cost the merge
-// 0.5 us.
+// workgroup per CU, down to one key group per wave where that pays (scan_floor): bound
+// by the key stream for long pasts, by a few round trips for short ones.  16,384 keys of
+// width 768: 18.4 -> 7.8 us against ranges of at least 64 keys per wave (64 workgroups);
+// 32 rows of 1,000 keys of width 1,024: 22.6 -> 14.4 us.  The lists this adds (up to
+// 1,024 per row) cost the merge 0.5 us at k = 8.
 // GUMBEL: the lists rank (and hold) score + Gumbel noise; the decode attention
 // recomputes the chosen chunks' raw scores.  Q8 (D = 512, eight column blocks
 // per key): every lane keeps its eight query fragments in registers, so there

@@ -44,12 +44,15 @@ def source_hash() -> str:
 
 def short_name(kernel: str) -> str:
     # forms that the library launches under one name
-    for form, key in (("xattn_fwd_wave_kernel", "xattn_fwd_kernel"), ("bwd_dq_few_kernel", "bwd_dq_kernel")):
+    for form, key in (("xattn_fwd_wave_kernel", "xattn_fwd_kernel"), ("bwd_dq_few_kernel", "bwd_dq_kernel"),
+                      ("dlmk_k_rows_kernel", "dlmk_k_kernel")):
         if form in kernel:
             return key
     for key in ("xattn_fwd_kernel", "bwd_dq_kernel", "bwd_dkdv_kernel", "chunk_scores_kernel", "topk_kernel",
                 "fused_select_kernel", "sel_clear_kernel", "select_part_kernel", "select_wide_kernel", "select_merge_kernel",
-                "decode_scan_kernel", "xattn_decode_kernel", "bwd_prep_kernel", "dsel_kernel", "dlmk_q_kernel", "dlmk_k_kernel"):
+                "decode_scan_kernel", "xattn_decode_kernel", "bwd_prep_kernel", "bwd_prep_clear_kernel", "bwd_prep_count_kernel",
+                "bwd_prep_scan_kernel", "bwd_prep_fill_kernel", "bwd_prep_sort_kernel", "dsel_kernel", "dlmk_q_kernel",
+                "dlmk_k_kernel"):
         if key in kernel:
             return key
     if "copy" in kernel.lower():
