@@ -530,11 +530,15 @@ __global__ __launch_bounds__(kThreads, (ONE ? 2 : kWgPerCu)) void xattn_fwd_kern
 // it gets denser); the copies are waited for 8 % of a tile's time.
 // Measured, MI355X, the launch alone, pair form above -> this: 64K tokens (B = 2,
 // H = 16, k = 8) 549 -> 487 us, 16K (B = 8, H = 12) 459 -> 411 us, 1M (H = 8, bound by
-// the gather past the L2) 2,580 -> 2,540 us.  One wave per SIMD (512 registers, tiles two
-// ahead, every product under a softmax) took 524 and 410 us: nothing hides a chunk
-// switch there.  Lists longer than kWaveMaxK stay with the pair form: their
-// log-sum-exps do not fit in LDS beside the tiles (8 x 20 KiB per CU), and storing them
-// per item made this form no faster (k = 16: 339 us against 336 us).
+// the gather past the L2) 2,580 -> 2,540 us.  Few chunks (12 heads, k = 8): 528 16.8 ->
+// 15.4 us, 768 17.2 -> 16.7, 1,032 23.6 -> 24.2, 1,200 24.2 -> 24.7, 1,536 30.5 -> 26.0,
+// 2,400 44.3 -> 40.0, 6,144 97 -> 84, 24,576 404 -> 374; k = 1 to 4 alike.  It loses where
+// its 2,048 waves start a pass that the pair form's 1,024 pairs have just finished: 3,120
+// 49.3 -> 52.7, 3,360 55.8 -> 51.7.
+// One wave per SIMD (512 registers, tiles two ahead, every product under a softmax) took
+// 524 and 410 us: nothing hides a chunk switch there.  Lists longer than kWaveMaxK stay
+// with the pair form: their log-sum-exps do not fit in LDS beside the tiles (8 x 20 KiB per
+// CU), and storing them per item made this form no faster (k = 16: 339 us against 336 us).
 constexpr int kWaveMaxK = 8;
 constexpr int kWavesPerCu = 8;
 template <bool OBO>
