@@ -748,8 +748,8 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void bwd_dq_kernel(BwdParams p,
         ox1 = 0.f;
       }
       if constexpr (STAGE) {
-        // this wave's staged values (its own LDS writes, read back in program
-        // order): per valid slot one contiguous run of 32 tokens
+        // this wave's staged values: per valid slot one contiguous run of 32 tokens
+        wave_lds_order();  // other lanes staged them ...
         for (int e = lane; e < 32 * K; e += 64) {
           const int sl = e >> 5, q = e & 31;
           if (sJ[pair][buf][sl] >= 0) {
@@ -762,6 +762,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void bwd_dq_kernel(BwdParams p,
           const int sl = opaque(lane);
           p.ws.dwp[(tglob * K + sl) * 2 + xh] = sJ[pair][buf][lane] >= 0 ? sDw[wave][lane] : 0.f;
         }
+        wave_lds_order();  // ... and the next chunk's are staged after this
       } else if (has_row && n < K && lane < K && sJ[pair][buf][lane] < 0) {
         const int sl = opaque(lane);
         p.ws.dwp[(tglob * K + sl) * 2 + xh] = 0.f;

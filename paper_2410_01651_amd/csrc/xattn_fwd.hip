@@ -459,10 +459,12 @@ __global__ __launch_bounds__(kThreads, (ONE ? 2 : kWgPerCu)) void xattn_fwd_kern
         // this wave's tokens are one contiguous run of 32 k entries; slots
         // without a chunk read -inf
         const int64_t base = (tok0 + 32 * half) * K;
+        wave_lds_order();  // other lanes' log-sum-exps ...
         for (int e = lane; e < 32 * K; e += 64) {
           const int tk = e / K, sl = e - tk * K;
           p.lse[base + e] = sJ[pair][buf][sl] < 0 ? -INFINITY : sLse[wave][tk][sl];
         }
+        wave_lds_order();  // ... which the next chunk's overwrite after this
       } else if (p.lse && n < K && hh == 0) {
         float* lse = p.lse + (tok0 + qi) * K;
         for (int s = 0; s < K; ++s)
