@@ -575,6 +575,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void bwd_dq_kernel(BwdParams p,
       const float wpx = __builtin_amdgcn_exp2f(fmaf(xs, sc, -offx));
       Dx = sum64(wpx * xdp) * __builtin_amdgcn_rcpf(wsf);
       sX[0].p[xh][lane] = (T)(wpx * (xdp - Dx));
+      wave_lds_order();  // one from each lane ...
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
         __builtin_amdgcn_sched_barrier(0);  // one key block's fragments live at a time
@@ -590,6 +591,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) void bwd_dq_kernel(BwdParams p,
         ox0 = frag_dot(k0, xf, ox0);
         ox1 = frag_dot(k1, xf, ox1);
       }
+      wave_lds_order();  // ... which the next slot's overwrite after this
       if (lane == 0) {
         sX[0].dl[0][s] = -Dx;
         sX[0].dl[1][s] = lse_x * kLog2e - __builtin_amdgcn_logf(ws);

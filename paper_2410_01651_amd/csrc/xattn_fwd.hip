@@ -356,8 +356,8 @@ __global__ __launch_bounds__(kThreads, (ONE ? 2 : kWgPerCu)) void xattn_fwd_kern
     }
     if (xr) {
       // LMK row output: (w P) V against the V^T fragments, read again now that
-      // the products have taken theirs (this wave's own probability writes are
-      // read back in program order)
+      // the products have taken theirs
+      wave_lds_order();  // the probabilities, one from each lane ...
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
         __builtin_amdgcn_sched_barrier(0);  // one key block's fragments live at a time
@@ -373,6 +373,7 @@ __global__ __launch_bounds__(kThreads, (ONE ? 2 : kWgPerCu)) void xattn_fwd_kern
         ox0 = frag_dot(v0, xf, ox0);
         ox1 = frag_dot(v1, xf, ox1);
       }
+      wave_lds_order();  // ... which the next slot's overwrite after this
     }
   };
 
