@@ -104,7 +104,7 @@ def test_forward_streams_ending_in_empty_chunks(dev, B, H, nC, first_empty):
 
 @pytest.mark.parametrize("dtype,D,nC,k,gumbel", [
     ("bf16", 576, 1, 3, False),
-    ("bf16", 1024, 129, 8, False),       # two row blocks, the second of one row; a ragged second key tile
+    ("bf16", 1024, 129, 8, False),       # few chunks: one pass with and without room for the lists
     ("bf16", 640, 1100, 16, True),
     ("bf16", 576, 9100, 5, False),       # several parts per class
     ("fp32", 320, 700, 8, True),
@@ -137,13 +137,13 @@ def test_wide_select_equals_score_matrix(dev, dtype, D, nC, k, gumbel):
 
 @pytest.mark.parametrize("dtype,D,nC,k,gumbel", [
     ("bf16", 64, 300, 8, False), ("bf16", 512, 150, 16, True), ("fp32", 256, 200, 5, False),   # queries in registers
-    ("bf16", 576, 300, 8, False), ("bf16", 1024, 150, 16, True), ("fp32", 320, 200, 5, False),  # both through LDS
-    ("bf16", 1024, 290, 16, True), ("fp32", 320, 260, 5, False),
+    ("bf16", 576, 300, 8, False), ("bf16", 1024, 150, 16, True), ("fp32", 320, 200, 5, False),  # both through LDS,
+    ("bf16", 1024, 290, 16, True), ("fp32", 320, 260, 5, False),                                # from 256 chunks
 ])
 def test_select_without_matrix_takes_finite_scores_only(dev, dtype, D, nC, k, gumbel):
     """Scores that overflow to +inf and -inf are no candidates, in rows with and without k finite
     ones, for every form of the selection.  (Wide landmarks run one pass when the output overlaps
-    an input; narrow ones only for k > 16.)"""
+    an input or the chunks are few; narrow ones only for k > 16.)"""
     import torch
     from paper_2410_01651_amd import gca
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
