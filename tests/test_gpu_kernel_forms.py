@@ -482,7 +482,7 @@ def test_fp32_backward_time_of_one_slot(dev):
     """Lists of one entry give four wave pairs per chunk nothing to share: two chunks per CU
     take 0.64 of the time of three (0.83 with four pairs per chunk)."""
     cus = _cus()
-    assert _fp32_step(dev, 2 * cus // 12 * 12, 1, True) <= 0.73 * _fp32_step(dev, 3 * cus // 12 * 12, 1, True)
+    assert _fp32_step(dev, 2 * cus // 12 * 12, 1, True) <= 0.75 * _fp32_step(dev, 3 * cus // 12 * 12, 1, True)
 
 
 @pytest.mark.parametrize("mode", ["causal", "decode"])
